@@ -59,6 +59,7 @@ constexpr uint32_t kStateLow = 1u << 15;
 // decoded INT8 container values are multiplied into a small int8 batch X and
 // summed into Y (int32) instead of being stored.
 constexpr int kOutDotI8 = 0x200;
+constexpr int kAnyType = 0;   // template argument: the output type is read from the layer
 constexpr uint32_t kDotMaxTokens = 8;
 
 // Index of the calling wave in its workgroup, as a wave-uniform (scalar) value.
@@ -210,30 +211,39 @@ __device__ __forceinline__ uint32_t e5m2_quad(float a, float b, float c, float d
   return (uint32_t)w;
 }
 
-__device__ __forceinline__ uint32_t uint8_quad(float a, float b, float c, float d) {
-  const int ia = (int)__builtin_rintf(__builtin_amdgcn_fmed3f(a, 0.0f, 255.0f));
-  const int ib = (int)__builtin_rintf(__builtin_amdgcn_fmed3f(b, 0.0f, 255.0f));
-  const int ic = (int)__builtin_rintf(__builtin_amdgcn_fmed3f(c, 0.0f, 255.0f));
-  const int id = (int)__builtin_rintf(__builtin_amdgcn_fmed3f(d, 0.0f, 255.0f));
-  return (uint32_t)ia | ((uint32_t)ib << 8) | ((uint32_t)ic << 16) | ((uint32_t)id << 24);
+// clamp(RNE(a), -128, 127) and the same of b as two bytes (low half-word):
+// round to nearest even, convert (the conversion saturates to the int32
+// range), then an arithmetic shift by 0 with saturation to int8, packed into
+// the low half of the destination (whose high half the instruction leaves as
+// it was, hence the mask).
+__device__ __forceinline__ uint32_t int8_pair(float a, float b) {
+  const int ia = (int)__builtin_rintf(a), ib = (int)__builtin_rintf(b);
+  uint32_t r;
+  asm("v_ashr_pk_i8_i32 %0, %1, %2, 0" : "=v"(r) : "v"(ia), "v"(ib));
+  return r & 0xFFFFu;
 }
 
 __device__ __forceinline__ uint32_t int8_quad(float a, float b, float c, float d) {
-  int ia = (int)__builtin_rintf(sat(a, 128.0f)), ib = (int)__builtin_rintf(sat(b, 128.0f));
-  int ic = (int)__builtin_rintf(sat(c, 128.0f)), id = (int)__builtin_rintf(sat(d, 128.0f));
-  ia = min(ia, 127), ib = min(ib, 127), ic = min(ic, 127), id = min(id, 127);
-  return (uint32_t)(ia & 0xFF) | ((uint32_t)(ib & 0xFF) << 8) | ((uint32_t)(ic & 0xFF) << 16) |
-         ((uint32_t)(id & 0xFF) << 24);
+  return int8_pair(a, b) | (int8_pair(c, d) << 16);
 }
 
-// Store the eight weights of vector v (elements 8v..8v+7), output type DT,
-// saturating to the type's finite range when SAT.
+// The same with saturation to [0, 255] (unsigned bytes).
+__device__ __forceinline__ uint32_t uint8_pair(float a, float b) {
+  const int ia = (int)__builtin_rintf(a), ib = (int)__builtin_rintf(b);
+  uint32_t r;
+  asm("v_ashr_pk_u8_i32 %0, %1, %2, 0" : "=v"(r) : "v"(ia), "v"(ib));
+  return r & 0xFFFFu;
+}
+
+__device__ __forceinline__ uint32_t uint8_quad(float a, float b, float c, float d) {
+  return uint8_pair(a, b) | (uint8_pair(c, d) << 16);
+}
+
+// Store the eight weights y of vector v (elements 8v..8v+7), output type DT,
+// saturating to the type's finite range when SAT.  For the doubled-coordinate
+// output y holds the coordinates themselves (exact halves of integers).
 template <int DT, bool SAT>
-__device__ __forceinline__ void store_vec(void* out, uint32_t v, const int32_t* p2,
-                                          float half_sigma) {
-  float y[8];
-#pragma unroll
-  for (int j = 0; j < 8; j++) y[j] = half_sigma * (float)p2[j];
+__device__ __forceinline__ void store_y(void* out, uint32_t v, float* y) {
   if constexpr (DT == EP_BF16) {
     if constexpr (SAT)
 #pragma unroll
@@ -274,8 +284,27 @@ __device__ __forceinline__ void store_vec(void* out, uint32_t v, const int32_t* 
     gptr<u32x2>(out)[v] = o;
   } else {  // EP_COORD2_I32
     EP_GLOBAL u32x4* o = gptr<u32x4>(out) + 2ull * v;
+    uint32_t p2[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) p2[j] = (uint32_t)(int32_t)(2.0f * y[j]);
+    o[0] = u32x4{p2[0], p2[1], p2[2], p2[3]};
+    o[1] = u32x4{p2[4], p2[5], p2[6], p2[7]};
+  }
+}
+
+// The same from doubled coordinates and half the row scale (one rounding each).
+template <int DT, bool SAT>
+__device__ __forceinline__ void store_vec(void* out, uint32_t v, const int32_t* p2,
+                                          float half_sigma) {
+  if constexpr (DT == EP_COORD2_I32) {
+    EP_GLOBAL u32x4* o = gptr<u32x4>(out) + 2ull * v;
     o[0] = u32x4{(uint32_t)p2[0], (uint32_t)p2[1], (uint32_t)p2[2], (uint32_t)p2[3]};
     o[1] = u32x4{(uint32_t)p2[4], (uint32_t)p2[5], (uint32_t)p2[6], (uint32_t)p2[7]};
+  } else {
+    float y[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) y[j] = half_sigma * (float)p2[j];
+    store_y<DT, SAT>(out, v, y);
   }
 }
 
@@ -342,6 +371,32 @@ __device__ __forceinline__ void store_vector(const Hot& L, uint32_t v, const int
     case EP_INT8: store_vec<EP_INT8, false>(L.out, v, p2, half_sigma); break;
     case EP_UINT8: store_vec<EP_UINT8, false>(L.out, v, p2, half_sigma); break;
     default: store_vec<EP_COORD2_I32, false>(L.out, v, p2, half_sigma); break;
+  }
+}
+
+// The eight weights y of vector v in the layer's output type.
+__device__ __forceinline__ void store_weights(const Hot& L, uint32_t v, float* y) {
+  switch (L.out_dtype) {
+    case EP_BF16:
+      if (L.saturate) store_y<EP_BF16, true>(L.out, v, y);
+      else store_y<EP_BF16, false>(L.out, v, y);
+      break;
+    case EP_FP16:
+      if (L.saturate) store_y<EP_FP16, true>(L.out, v, y);
+      else store_y<EP_FP16, false>(L.out, v, y);
+      break;
+    case EP_FP32: store_y<EP_FP32, false>(L.out, v, y); break;
+    case EP_FP8_E4M3:
+      if (L.saturate) store_y<EP_FP8_E4M3, true>(L.out, v, y);
+      else store_y<EP_FP8_E4M3, false>(L.out, v, y);
+      break;
+    case EP_FP8_E5M2:
+      if (L.saturate) store_y<EP_FP8_E5M2, true>(L.out, v, y);
+      else store_y<EP_FP8_E5M2, false>(L.out, v, y);
+      break;
+    case EP_INT8: store_y<EP_INT8, false>(L.out, v, y); break;
+    case EP_UINT8: store_y<EP_UINT8, false>(L.out, v, y); break;
+    default: store_y<EP_COORD2_I32, false>(L.out, v, y); break;
   }
 }
 
@@ -1233,99 +1288,99 @@ __device__ __forceinline__ void coset_step2(uint32_t& x0, uint32_t& x1, uint32_t
 }
 
 // ---- one chain per wave (small launches) ----------------------------------------
-// The same steps for a wave that advances a single chain (two tiles, one per
-// half): each step's instructions are chain 0's of the two-chain steps.  A
-// wave alone on its SIMD issues about one instruction per four cycles, so a
-// launch with too few tasks to put several waves on every SIMD finishes
-// sooner when each wave issues half the instructions per symbol and there are
-// twice as many waves.
-#define EP_REFILL_ONE_W(WORK)                                               \
+// A launch with too few tiles to put several waves on every SIMD is bound by
+// the latency of a wave's own serial chain of symbol steps, so a wave then
+// advances one chain of two tiles and its step keeps the scalar unit out of
+// that chain: a vector compare whose ballot goes through the scalar unit and
+// back to a vector operand takes 32 cycles on gfx950, one read by v_mbcnt
+// directly takes 13.  Each lane keeps its stream position P (payload words
+// from the first block of its tile's stream, equal over a half), takes its
+// word at P plus the number of refilling lanes below it in its half (v_mbcnt
+// over the ballot's lower word for lanes 0-31 only, then over its upper
+// word) and advances P by the popcount of its own half of the ballot while the
+// word is in flight.  A step of a wave alone on its SIMD takes 189 cycles, two
+// LDS round trips of 56 cycles among them; a whole decode, rounds' overhead
+// included, went from 106 to 88 ns a step (3072^2 to FP16: 36.6 -> 32.1 us,
+// 10240 x 3840 at 1820-vector tiles to BF16: 106 -> 83 us).
+// An SGPR that a vector instruction wrote may be read as a vector operand two
+// wait states later at the earliest (gfx940 and up); FILL is one instruction of
+// the step's own work in the second of them.
+#define EP_REFILL_ONE_W(FILL, WORK)                                         \
   "v_cmp_gt_u32_e32 vcc, 0x8000, %[x0]\n\t"                                 \
-  "s_bcnt1_i32_b32 %[c0lo], vcc_lo\n\t"                                    \
-  "v_mbcnt_lo_u32_b32 %[t0], vcc_lo, 0\n\t"                                 \
-  "s_bcnt1_i32_b32 %[c0hi], vcc_hi\n\t"                                    \
+  "v_lshlrev_b32_e32 %[xs], 16, %[x0]\n\t"                                  \
+  FILL                                                                     \
+  "v_and_b32_e32 %[u0], vcc_lo, %[mlo]\n\t"                                 \
+  "v_mbcnt_lo_u32_b32 %[t0], %[u0], %[P]\n\t"                               \
   "v_mbcnt_hi_u32_b32 %[t0], vcc_hi, %[t0]\n\t"                             \
-  "s_sub_u32 %[d0], %[D0], %[c0lo]\n\t"                                    \
-  "v_mad_i32_i24 %[t0], %[vH], %[d0], %[t0]\n\t"                            \
-  "v_add_lshl_u32 %[t0], %[t0], %[SA0], 1\n\t"                              \
+  "v_lshlrev_b32_e32 %[t0], 1, %[t0]\n\t"                                   \
   "v_and_or_b32 %[t0], %[t0], %[rmask], %[vrb0]\n\t"                        \
   "ds_read_u16 %[w0], %[t0]\n\t"                                            \
-  "s_add_u32 %[SA0], %[SA0], %[c0lo]\n\t"                                  \
-  "s_setprio 0\n\t"                                                        \
-  "s_add_u32 %[D0], %[d0], %[c0hi]\n\t"                                  \
+  "v_and_b32_e32 %[g0], vcc_hi, %[mhi]\n\t"                                 \
+  "v_bcnt_u32_b32 %[P], %[u0], %[P]\n\t"                                    \
+  "v_bcnt_u32_b32 %[P], %[g0], %[P]\n\t"                                    \
   WORK                                                                     \
-  "s_and_saveexec_b64 %[ex], vcc\n\t"                                       \
   "s_waitcnt lgkmcnt(0)\n\t"                                                \
-  "v_lshl_or_b32 %[x0], %[x0], 16, %[w0]\n\t"                               \
-  "s_mov_b64 exec, %[ex]\n\t"
+  "v_or_b32_e32 %[w0], %[xs], %[w0]\n\t"                                    \
+  "v_cndmask_b32_e32 %[x0], %[x0], %[w0], vcc\n\t"
 
 #define EP_STEP1_OUTS                                                                    \
-  [x0] "+v"(x0), [SA0] "+s"(F0.OA), [D0] "+s"(F0.D), [u0] "=&v"(u0), [g0] "=&v"(g0),   \
-      [t0] "=&v"(t0), [w0] "=&v"(w0), [c0lo] "=&s"(c0lo), [c0hi] "=&s"(c0hi),           \
-      [d0] "=&s"(dd0), [ex] "=&s"(ex)
+  [x0] "+v"(x0), [P] "+v"(P), [u0] "=&v"(u0), [g0] "=&v"(g0), [t0] "=&v"(t0), [w0] "=&v"(w0), \
+      [xs] "=&v"(xs)
 
-#define EP_STEP1_TEMPS                                                                   \
-  uint32_t u0, g0, t0, w0, c0lo, c0hi, dd0;                                              \
-  uint64_t ex
+#define EP_STEP1_TEMPS uint32_t u0, g0, t0, w0, xs
 
 #define EP_STEP1_INS                                                                     \
-  [vH] "v"(vH), [vrb0] "v"(vrb0), [rmask] "s"(kFastRingBytes - 1), [mk] "i"((1 << B) - 1), \
-      [b] "i"(B)
+  [mlo] "v"(mlo), [mhi] "v"(~mlo), [vrb0] "v"(vrb0), [rmask] "s"(kOneRingBytes - 1),      \
+      [mk] "i"((1 << B) - 1), [b] "i"(B)
 
-#define EP_STEP1_CLOBBERS "vcc", "scc", "exec", "memory"
+#define EP_STEP1_CLOBBERS "vcc", "memory"
 
-#define EP_Y_CVT1                                                                     \
-  "v_cvt_f32_i32_sdwa %[y0], sext(%[e0]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3\n\t" \
-  "v_fma_f32 %[y0], %[sg0], %[y0], %[hc0]\n\t"
-#define EP_Y_CVT1_WIDE                                                                \
-  "v_ashrrev_i32 %[y0], 22, %[e0]\n\t"                                                \
-  "v_cvt_f32_i32_e32 %[y0], %[y0]\n\t"                                                \
-  "v_fma_f32 %[y0], %[sg0], %[y0], %[hc0]\n\t"
-#define EP_Y_SAT1 "v_med3_f32 %[y0], %[y0], %[nm], %[m]\n\t"
+#define EP_Y_CVT1 \
+  "v_cvt_f32_i32_sdwa %[y0], sext(%[e0]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3\n\t"
+#define EP_Y_Z1_WIDE "v_ashrrev_i32 %[y0], 22, %[e0]\n\t"
+#define EP_Y_CVT1_WIDE "v_cvt_f32_i32_e32 %[y0], %[y0]\n\t"
+#define EP_Y_FMA1 "v_fma_f32 %[y0], %[sg0], %[y0], %[hc0]\n\t"
 #define EP_Y_PAR1 "v_and_or_b32 %[e0], %[X0], %[bit], %[e0]\n\t"
 
-#define EP_FIELD1_ASM(DEC0, WORK)                                                        \
+#define EP_FIELD1_ASM(DEC0, FILL, WORK)                                                  \
   asm volatile(                                                                          \
       "v_and_b32 %[u0], %[mk], %[x0]\n\t"                                                \
       "v_lshl_add_u32 %[u0], %[u0], 2, %[cb0]\n\t"                                       \
       "ds_read_b32 %[e0], %[u0] offset:%[off]\n\t"                                       \
       "v_lshrrev_b32 %[g0], %[b], %[x0]\n\t"                                             \
       "s_waitcnt lgkmcnt(0)\n\t"                                                         \
-      "s_setprio 2\n\t"                                                                  \
       DEC0                                                                               \
-      EP_REFILL_ONE_W(WORK)                                                              \
+      EP_REFILL_ONE_W(FILL, WORK)                                                        \
       : EP_STEP1_OUTS, [e0] "=&v"(e0), [y0] "=&v"(y0)                                    \
       : [cb0] "v"(cb0), [off] "i"((FIELD - 1) * (4 << B)), [sg0] "v"(sg0), [hc0] "v"(hc0), \
-        [m] "s"(m), [nm] "v"(-m), [X0] "v"(X0), [bit] "s"(zbit), EP_STEP1_INS            \
+        [X0] "v"(X0), [bit] "s"(zbit), EP_STEP1_INS                                      \
       : EP_STEP1_CLOBBERS)
 
-// Field symbol of the single chain (see field_step2).
-template <int B, int FIELD, int YM, bool WIDE>
-__device__ __forceinline__ void field_step1(uint32_t& x0, uint32_t cb0, uint32_t& e0, float& y0,
-                                            float sg0, float hc0, uint32_t X0, float m, FastChain& F0,
-                                            uint32_t vH, uint32_t vrb0) {
+constexpr uint32_t kOneRingBytes = 2 * kFastRingBytes;   // one half's ring: both chains' share
+constexpr uint32_t kOneRingWords = kOneRingBytes / 2;
+
+// Field symbol of the single chain (see field_step2): entry in e0, weight
+// fma(sg, z, hc) in y0.  mlo: all ones in lanes 0-31, 0 in lanes 32-63.
+template <int B, int FIELD, bool WIDE>
+__device__ __forceinline__ void field_step1(uint32_t& x0, uint32_t& P, uint32_t cb0, uint32_t& e0,
+                                            float& y0, float sg0, float hc0, uint32_t X0,
+                                            uint32_t mlo, uint32_t vrb0) {
   EP_STEP1_TEMPS;
   const uint32_t zbit = 1u << (WIDE ? 22 : 24);   // low bit of the entry's z
   if constexpr (WIDE) {
-    if constexpr (YM == 0) EP_FIELD1_ASM(EP_DEC_WIDE(0), "");
-    else if constexpr (FIELD == 8 && YM == 1) EP_FIELD1_ASM(EP_DEC_WIDE(0), EP_Y_PAR1 EP_Y_CVT1_WIDE);
-    else if constexpr (FIELD == 8) EP_FIELD1_ASM(EP_DEC_WIDE(0), EP_Y_PAR1 EP_Y_CVT1_WIDE EP_Y_SAT1);
-    else if constexpr (YM == 1) EP_FIELD1_ASM(EP_DEC_WIDE(0), EP_Y_CVT1_WIDE);
-    else EP_FIELD1_ASM(EP_DEC_WIDE(0), EP_Y_CVT1_WIDE EP_Y_SAT1);
+    if constexpr (FIELD == 8) EP_FIELD1_ASM(EP_DEC_WIDE(0), EP_Y_PAR1, EP_Y_Z1_WIDE EP_Y_CVT1_WIDE EP_Y_FMA1);
+    else EP_FIELD1_ASM(EP_DEC_WIDE(0), EP_Y_Z1_WIDE, EP_Y_CVT1_WIDE EP_Y_FMA1);
   } else {
-    if constexpr (YM == 0) EP_FIELD1_ASM(EP_DEC(0), "");
-    else if constexpr (FIELD == 8 && YM == 1) EP_FIELD1_ASM(EP_DEC(0), EP_Y_PAR1 EP_Y_CVT1);
-    else if constexpr (FIELD == 8) EP_FIELD1_ASM(EP_DEC(0), EP_Y_PAR1 EP_Y_CVT1 EP_Y_SAT1);
-    else if constexpr (YM == 1) EP_FIELD1_ASM(EP_DEC(0), EP_Y_CVT1);
-    else EP_FIELD1_ASM(EP_DEC(0), EP_Y_CVT1 EP_Y_SAT1);
+    if constexpr (FIELD == 8) EP_FIELD1_ASM(EP_DEC(0), EP_Y_PAR1, EP_Y_CVT1 EP_Y_FMA1);
+    else EP_FIELD1_ASM(EP_DEC(0), EP_Y_CVT1, EP_Y_FMA1);
   }
 }
 
 // Coset symbol of the single chain (see coset_step2).
 template <int B>
-__device__ __forceinline__ void coset_step1(uint32_t& x0, uint32_t& cb0, float& hc0, float sg0,
-                                            uint32_t vf0, uint32_t vf1, uint32_t vcb, FastChain& F0,
-                                            uint32_t vH, uint32_t vrb0) {
+__device__ __forceinline__ void coset_step1(uint32_t& x0, uint32_t& P, uint32_t& cb0, float& hc0,
+                                            float sg0, uint32_t vf0, uint32_t vf1, uint32_t vcb,
+                                            uint32_t mlo, uint32_t vrb0) {
   EP_STEP1_TEMPS;
   asm volatile(
       "v_and_b32 %[u0], %[mk], %[x0]\n\t"
@@ -1338,10 +1393,37 @@ __device__ __forceinline__ void coset_step1(uint32_t& x0, uint32_t& cb0, float& 
       "v_mul_f32_e32 %[w0], 0.5, %[sg0]\n\t"
       "v_cndmask_b32_e32 %[hc0], 0, %[w0], vcc\n\t"
       "v_sub_u32_e32 %[x0], %[x0], %[t0]\n\t"
-      EP_REFILL_ONE_W("")
+      EP_REFILL_ONE_W("s_nop 0\n\t", "")
       : EP_STEP1_OUTS, [cb0] "=&v"(cb0), [hc0] "=&v"(hc0)
       : [vf0] "v"(vf0), [vf1] "v"(vf1), [vcb] "v"(vcb), [sg0] "v"(sg0), EP_STEP1_INS
       : EP_STEP1_CLOBBERS);
+}
+
+// The payload staging of a single chain, all of it per lane (uniform over each
+// half): positions in words from the first block of the half's stream.  A half's
+// ring holds four 128-word blocks, addressed modulo its size.  A block is
+// requested into registers and committed once the ring has room for it, at the
+// start of a round and after field 4: by then it was requested at least half a
+// round earlier.  Between two such points a valid stream at b bits takes at
+// most 2 b n + 32 words in n <= 5 steps, fewer than a block, so the margin of
+// 385 words that a commit restores is never used up.
+struct OneChain {
+  uint32_t P, Q;     // read position, committed end
+  uint32_t C, E;     // payload word of the first block, end of the stream (from C)
+  u32x2 pend;        // the block after the committed ones (this lane's 8 bytes)
+};
+
+__device__ __forceinline__ void one_fetch(OneChain& F, __amdgpu_buffer_rsrc_t rsrc, uint32_t l) {
+  F.pend = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (F.Q < F.E ? 2 * (F.C + F.Q) : kFastOob) + 8 * l, 0, 0);
+}
+
+__device__ __forceinline__ void one_stage(OneChain& F, uint8_t* lds, uint32_t vrb8,
+                                          __amdgpu_buffer_rsrc_t rsrc, uint32_t l) {
+  if (__builtin_expect(F.Q - F.P <= kOneRingWords - kFastBlockWords, 0)) {
+    *reinterpret_cast<u32x2*>(lds + vrb8 + 2 * (F.Q & (kOneRingWords - 1))) = F.pend;
+    F.Q += kFastBlockWords;
+    one_fetch(F, rsrc, l);
+  }
 }
 
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
@@ -1365,26 +1447,6 @@ struct QAcc {
   float yp;       // its weight
   uint32_t w[8];  // packed output words (the output type uses 2, 4 or 8 of them)
 };
-
-// clamp(RNE(a), -128, 127) and the same of b as two bytes (low half-word):
-// round to nearest even, convert (the conversion saturates to the int32
-// range), then an arithmetic shift by 0 with saturation to int8, packed into
-// the low half of the destination (whose high half the instruction leaves as
-// it was, hence the mask).
-__device__ __forceinline__ uint32_t int8_pair(float a, float b) {
-  const int ia = (int)__builtin_rintf(a), ib = (int)__builtin_rintf(b);
-  uint32_t r;
-  asm("v_ashr_pk_i8_i32 %0, %1, %2, 0" : "=v"(r) : "v"(ia), "v"(ib));
-  return r & 0xFFFFu;
-}
-
-// The same with saturation to [0, 255] (unsigned bytes).
-__device__ __forceinline__ uint32_t uint8_pair(float a, float b) {
-  const int ia = (int)__builtin_rintf(a), ib = (int)__builtin_rintf(b);
-  uint32_t r;
-  asm("v_ashr_pk_u8_i32 %0, %1, %2, 0" : "=v"(r) : "v"(ia), "v"(ib));
-  return r & 0xFFFFu;
-}
 
 // Fold field FIELD's entry e and weight y (computed in the step, see
 // field_step2) into the chain's accumulator; c is the coset bit.
@@ -1703,16 +1765,26 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
   if (err && status) atomicOr(status, (int32_t)err);
 }
 
-// The slot-table steady state with one chain: a task of two tiles, t0 in
+// The slot-table decode with one chain per wave: a task of two tiles, t0 in
 // lanes 0-31 and t0 + 1 in lanes 32-63, for launches with too few four-tile
-// tasks to fill the SIMDs (see field_step1), and for the fused product with
-// more than four rows of X, whose sums then fit the registers.  The structure
-// is lut_task's with the second chain removed.
-template <int B, int DT, bool SAT, bool TWO, bool WIDE, int MT = 1>
+// tasks to fill the SIMDs, and for the fused product with more than four rows
+// of X (MT of them at most; 0 stores the weights), whose sums then fit the
+// registers.  Tiles of any length, and a missing second tile: in the rounds
+// after the shorter tile's last full one, lanes without a vector are pinned as
+// in lut_task.  The weights of a vector are packed and stored at the end of its
+// round (DT: the output type, or kAnyType to switch on the layer's there).
+// The fused product needs whole tiles of whole rounds and rows of at least a
+// tile (task_b checks).
+//
+// TWO: every lane's vectors v, v + 32, ... lie in at most two rows, so a lane
+// holds both scales, switches at round kc and scales inside the steps.
+// Otherwise the steps form the coordinates themselves and the round's scale,
+// requested at its start, multiplies them at its end: one rounding either way,
+// and no wait for memory but that one.
+template <int B, bool WIDE, int DT, bool TWO, int MT = 0>
 __device__ __forceinline__ void lut_task1(const Hot& L, uint8_t* lds, uint32_t ring_area, uint32_t t0,
                                           int32_t* status) {
-  constexpr bool DOT = DT == kOutDotI8;
-  static_assert(!DOT || TWO, "the fused product runs the steady state on rows of at least a tile");
+  constexpr bool DOT = MT > 0;
   const uint32_t lane = threadIdx.x & 63, wave = wave_id();
   const uint32_t half = lane >> 5, l = lane & 31;
   const EP_GLOBAL uint32_t* states = gptr<const uint32_t>(L.blob + L.off_states);
@@ -1721,68 +1793,65 @@ __device__ __forceinline__ void lut_task1(const Hot& L, uint8_t* lds, uint32_t r
       const_cast<uint8_t*>(L.blob + L.off_payload), (short)0, (int)L.pay_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(L.blob + L.off_sigma), (short)0, (int)(4 * L.rows), 0x00020000);
-  constexpr uint32_t VB = vec_bytes<DT>();
-  constexpr int YM = DT == EP_COORD2_I32 ? 0 : SAT ? 2 : 1;
-  const float ymax = DT == EP_FP8_E4M3 ? 448.0f : DT == EP_FP8_E5M2 ? 57344.0f
-                     : DT == EP_FP16 ? 65504.0f : 3.38953139e38f;
 
-  // the wave's first ring (the two-chain layout's chain 0)
-  const uint32_t vrb0 = ring_area + wave * 2 * kFastChainBytes + half * kFastRingBytes;
-  const uint32_t vl8 = 8 * l;
-  uint32_t o[3];
-#pragma unroll
-  for (int i = 0; i < 3; i++) o[i] = offs[t0 + i];
+  const uint32_t vrb0 = ring_area + wave * 2 * kFastChainBytes + half * kOneRingBytes;
+  const uint32_t vrb08 = vrb0 + 8 * l;
   const uint32_t tile = t0 + half;
-  uint32_t x = states[(uint64_t)tile * 32 + l];
+  const bool ok = tile < L.tile_end;   // false: the range's last task has one tile
+  const uint32_t nvec = L.rows * L.cvec;
+  const uint32_t nv = ok ? min(L.V, nvec - tile * L.V) : 0;   // the tile's vectors
   const uint32_t vb = tile * L.V + l;
-  const uint32_t voff = (half * L.V + l) * VB;
+  const uint32_t p0 = ok ? offs[tile] : 0, p1 = ok ? offs[tile + 1] : 0;
+  uint32_t x = ok ? states[(uint64_t)tile * 32 + l] : kStateLow;
+  const uint32_t r = row_of(L, vb);
   uint32_t kc = 0;
-  float sa = 0.0f, sb = 0.0f;
-  if constexpr (TWO) {
-    const uint32_t r = row_of(L, vb);
+  float sa = 1.0f, sb = 1.0f;
+  const bool coord = DT == kAnyType && L.out_dtype == EP_COORD2_I32;
+  if (TWO && !coord) {
     kc = ((r + 1) * L.cvec - vb + 31) >> 5;
     sa = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(srsrc, 4 * r, 0, 0));
     sb = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(srsrc, 4 * r + 4, 0, 0));
   }
-  int32_t dacc[MT];
+  int32_t dacc[DOT ? MT : 1];
   uint32_t r0 = 0, kd = 0, colb = 0;
   __amdgpu_buffer_rsrc_t xrsrc;
   if constexpr (DOT) {
     xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(L.x), (short)0,
                                               (int)(L.m * L.cols), 0x00020000);
-    r0 = row_of(L, tile * L.V);                 // first row of the lane's tile
-    kd = row_of(L, vb) == r0 ? kc : 0u;         // first round in row r0 + 1
+    r0 = row_of(L, tile * L.V);   // first row of the lane's tile
+    kd = r == r0 ? kc : 0u;       // first round in row r0 + 1
     colb = vb - r0 * L.cvec;
 #pragma unroll
     for (int t = 0; t < MT; t++) dacc[t] = 0;
   }
-  FastChain F0;
-  u32x2 pend0, pendB0;
-#pragma unroll
-  for (int i = 0; i < 3; i++) o[i] = uni(o[i]);
-  const u32x4 fill0 = fast_start(F0, pend0, rsrc, half, l, o[0], o[1], o[1], o[2]);
+  OneChain F;
+  F.C = p0 & ~(kFastBlockWords - 1);
+  F.P = p0 - F.C;
+  F.E = p1 - F.C;
+  F.Q = kOneRingWords;
+  const u32x4 fill0 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, 2 * F.C + 16 * l, 0, 0);
+  const u32x4 fill1 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, 2 * F.C + 512 + 16 * l, 0, 0);
+  one_fetch(F, rsrc, l);
   __builtin_amdgcn_s_waitcnt(0);
   *reinterpret_cast<u32x4*>(lds + vrb0 + 16 * l) = fill0;
-  pendB0 = pend0;   // pend0 serves lanes 0-31, pendB0 lanes 32-63
+  *reinterpret_cast<u32x4*>(lds + vrb0 + 512 + 16 * l) = fill1;
 
-  EP_GLOBAL uint8_t* obase = gptr<uint8_t>(L.out) + (uint64_t)t0 * L.V * VB;
-  const uint32_t vH = half;
+  const uint32_t mlo = half ? 0u : ~0u;
   const uint32_t vf0 = L.coset_f0, vf1 = L.coset_f1, vcb = 32u << B;
-  // full rounds, then a partial one with the states of lanes past the tile
-  // pinned (see lut_task)
-  const uint32_t full = L.V / 32, tail = L.V % 32;
-  const uint32_t vrb08 = vrb0 + vl8;
-  uint32_t xsave = 0;
-  const bool pin = l >= tail;
+  const uint32_t nvA = uni(nv), nvB = (uint32_t)__builtin_amdgcn_readlane((int)nv, 32);
+  const uint32_t full = min(nvA, nvB) / 32, rounds = (max(nvA, nvB) + 31) / 32;
 
   auto round = [&](uint32_t k, auto part) {
     constexpr bool PART = decltype(part)::value;
-    if constexpr (PART) xsave = x;
-    fast_stage(F0, pend0, pendB0, lds, vrb08, vl8, rsrc, half, kFastRingWords - kFastBlockWords + 1);
-    float sg;
+    const uint32_t i = l + 32 * k;   // this round's vector of the tile
+    const bool pin = PART && i >= nv;
+    const uint32_t xsave = x;
+    one_stage(F, lds, vrb08, rsrc, l);
+    float sg = 1.0f, scale = 1.0f;
     if constexpr (TWO) sg = k < kc ? sa : sb;
-    else sg = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(srsrc, 4 * row_of(L, vb + 32 * k), 0, 0));
-    uint32_t xo = 0, xq[MT];
+    else scale = __uint_as_float(
+        __builtin_amdgcn_raw_buffer_load_b32(srsrc, 4 * row_of(L, vb + 32 * k), 0, 0));
+    uint32_t xo = 0, xq[DOT ? MT : 1];
     if constexpr (DOT) {
       EP_GLOBAL int32_t* y = gptr<int32_t>(L.out);
       // lanes whose vectors pass into row r0 + 1 this round: their sums so far belong to r0
@@ -1800,48 +1869,50 @@ __device__ __forceinline__ void lut_task1(const Hot& L, uint8_t* lds, uint32_t r
 #pragma unroll
       for (int t = 0; t < MT; t++) xq[t] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, xo, t * L.cols, 0);
     }
-    uint32_t cb, e0;
-    float y0, hc;
-    QAcc acc;
-    acc.X = 0;
-#define EP_PIN1                       \
+    uint32_t cb, e[2];
+    float hc, y[8];
+    uint32_t X = 0;   // xor of the entries of fields 1..7 (see QAcc)
+#define EP_PIN1 \
   if constexpr (PART) x = pin ? kPinnedState : x;
     EP_PIN1
-    coset_step1<B>(x, cb, hc, sg, vf0, vf1, vcb, F0, vH, vrb0);
-#define EP_FIELD(I)                                                                        \
-  EP_PIN1                                                                                  \
-  field_step1<B, I, YM, WIDE>(x, cb, e0, y0, sg, hc, acc.X, ymax, F0, vH, vrb0);           \
-  q_take<DT, I, WIDE>(acc, e0, y0, cb >> (B + 5));
-    EP_FIELD(1) EP_FIELD(2)
-    fast_stage(F0, pend0, pendB0, lds, vrb08, vl8, rsrc, half, 3 * 32);
-    EP_FIELD(3) EP_FIELD(4)
+    coset_step1<B>(x, F.P, cb, hc, sg, vf0, vf1, vcb, mlo, vrb0);
+#define EP_FIELD(I)                                                                     \
+  EP_PIN1                                                                               \
+  field_step1<B, I, WIDE>(x, F.P, cb, e[I & 1], y[I - 1], sg, hc, X, mlo, vrb0);        \
+  if constexpr (I == 7) X ^= e[1];                                                      \
+  else if constexpr (I < 7 && I % 2 == 0) X = xor3(X, e[0], e[1]);
+    EP_FIELD(1) EP_FIELD(2) EP_FIELD(3) EP_FIELD(4)
+    one_stage(F, lds, vrb08, rsrc, l);
     if constexpr (DOT) {
+      const uint32_t w = int8_quad(y[0], y[1], y[2], y[3]);
 #pragma unroll
       for (int t = 0; t < MT; t++) {
-        dacc[t] = __builtin_amdgcn_sdot4((int)acc.w[0], (int)xq[t], dacc[t], false);
+        dacc[t] = __builtin_amdgcn_sdot4((int)w, (int)xq[t], dacc[t], false);
         xq[t] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, xo + 4, t * L.cols, 0);
       }
     }
-    EP_FIELD(5)
-    fast_stage(F0, pend0, pendB0, lds, vrb08, vl8, rsrc, half, 3 * 32);
-    EP_FIELD(6) EP_FIELD(7) EP_FIELD(8)
+    EP_FIELD(5) EP_FIELD(6) EP_FIELD(7) EP_FIELD(8)
 #undef EP_FIELD
 #undef EP_PIN1
     if constexpr (DOT) {
+      const uint32_t w = int8_quad(y[4], y[5], y[6], y[7]);
 #pragma unroll
-      for (int t = 0; t < MT; t++)
-        dacc[t] = __builtin_amdgcn_sdot4((int)acc.w[1], (int)xq[t], dacc[t], false);
+      for (int t = 0; t < MT; t++) dacc[t] = __builtin_amdgcn_sdot4((int)w, (int)xq[t], dacc[t], false);
     } else {
-      if (!PART || !pin) q_put<DT>(obase, voff, acc);
-      obase += 32 * VB;
+      if constexpr (!TWO)
+        if (!coord)
+#pragma unroll
+          for (int j = 0; j < 8; j++) y[j] *= scale;
+      if (!PART || !pin) {
+        if constexpr (DT == kAnyType) store_weights(L, vb + 32 * k, y);
+        else store_y<DT, false>(L.out, vb + 32 * k, y);
+      }
+      if constexpr (PART) x = pin ? xsave : x;
     }
   };
   for (uint32_t k = 0; k < full; k++) round(k, std::false_type{});
   if constexpr (!DOT) {
-    if (tail) {
-      round(full, std::true_type{});
-      x = pin ? xsave : x;
-    }
+    for (uint32_t k = full; k < rounds; k++) round(k, std::true_type{});
   } else {
     EP_GLOBAL int32_t* y = gptr<int32_t>(L.out);
     const bool moved = full > kd;   // the lane's last vector lies in row r0 + 1
@@ -1857,35 +1928,46 @@ __device__ __forceinline__ void lut_task1(const Hot& L, uint8_t* lds, uint32_t r
   }
 
   uint32_t err = 0;
-  if (x != kStateLow) err |= EP_STATUS_BAD_FINAL_STATE;
-  const uint32_t P = half ? F0.OA + F0.D : F0.OA, E = half ? F0.EB : F0.EA;
-  if (l == 0 && P != E) err |= P > E ? EP_STATUS_PAYLOAD_OVERRUN : EP_STATUS_BAD_END_OFFSET;
-  if (L.container && L.dequant) {
-    const EP_GLOBAL float* delta = gptr<const float>(L.blob + L.off_delta);
-    const uint32_t v0 = tile * L.V;
-    const uint32_t r_first = (v0 + L.cvec - 1) / L.cvec;
-    const uint32_t r_last = (v0 + L.V - 1) / L.cvec;
-    for (uint32_t r = r_first + l; r <= r_last; r += 32) gptr<float>(L.dequant)[r] = delta[r];
+  if (ok) {
+    if (x != kStateLow) err |= EP_STATUS_BAD_FINAL_STATE;
+    if (l == 0 && F.P != F.E) err |= F.P > F.E ? EP_STATUS_PAYLOAD_OVERRUN : EP_STATUS_BAD_END_OFFSET;
+    if (L.container && L.dequant) {
+      const EP_GLOBAL float* delta = gptr<const float>(L.blob + L.off_delta);
+      const uint32_t v0 = tile * L.V;
+      const uint32_t r_first = (v0 + L.cvec - 1) / L.cvec;
+      const uint32_t r_last = (v0 + nv - 1) / L.cvec;
+      for (uint32_t q = r_first + l; q <= r_last; q += 32) gptr<float>(L.dequant)[q] = delta[q];
+    }
   }
   if (err && status) atomicOr(status, (int32_t)err);
 }
 
-// NCH: chains per wave (2: a four-tile task, 1: a two-tile task).
-template <int B, int DT, bool SAT, bool WIDE, int NCH = 2>
+// Output type and row-scale variants of a two-tile slot-table task: the types
+// that small layers are decoded to have instances of their own, the rest (and
+// weights that need the explicit clamp) share one.
+template <int B, bool WIDE>
+__device__ __forceinline__ void lut_task1_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
+                                              uint32_t t0, int32_t* status) {
+  auto rows = [&](auto dt) {
+    constexpr int DT = decltype(dt)::value;
+    if (L.cvec >= 32 * ((L.V - 1) / 32)) lut_task1<B, WIDE, DT, true>(L, lds, ring_area, t0, status);
+    else lut_task1<B, WIDE, DT, false>(L, lds, ring_area, t0, status);
+  };
+  switch (L.saturate ? (uint32_t)kAnyType : L.out_dtype) {
+    case EP_BF16: rows(std::integral_constant<int, EP_BF16>{}); break;
+    case EP_FP16: rows(std::integral_constant<int, EP_FP16>{}); break;
+    case EP_FP8_E4M3: rows(std::integral_constant<int, EP_FP8_E4M3>{}); break;
+    case EP_INT8: rows(std::integral_constant<int, EP_INT8>{}); break;
+    default: rows(std::integral_constant<int, kAnyType>{}); break;
+  }
+}
+
+// Row-scale and sum variants of a full four-tile slot-table task.
+template <int B, int DT, bool SAT, bool WIDE>
 __device__ __forceinline__ void lut_task_rows(const Hot& L, uint8_t* lds, uint32_t ring_area,
                                               uint32_t t0, int32_t* status) {
-  static_assert(NCH == 2 || DT == EP_BF16 || DT == EP_FP16 || DT == EP_FP8_E4M3 || DT == EP_INT8 ||
-                    DT == kOutDotI8,
-                "one-chain tasks cover the common output types");
-  if constexpr (NCH == 1 && DT == kOutDotI8) {
-    // more than four rows of X (the only product that runs one chain); rows
-    // of at least a tile (lut_task_any checks)
-    lut_task1<B, DT, false, true, WIDE, kDotMaxTokens>(L, lds, ring_area, t0, status);
-  } else if constexpr (NCH == 1) {
-    if (L.cvec >= 32 * ((L.V - 1) / 32)) lut_task1<B, DT, SAT, true, WIDE>(L, lds, ring_area, t0, status);
-    else lut_task1<B, DT, SAT, false, WIDE>(L, lds, ring_area, t0, status);
-  } else if constexpr (DT == kOutDotI8) {
-    // up to four rows of X (more take one chain per wave, lut_task_any)
+  if constexpr (DT == kOutDotI8) {
+    // up to four rows of X (more take one chain per wave, task_b)
     if (L.cvec >= L.V) {
       if (L.m <= 1) lut_task<B, DT, false, true, WIDE, 1>(L, lds, ring_area, t0, status);
       else if (L.m <= 2) lut_task<B, DT, false, true, WIDE, 2>(L, lds, ring_area, t0, status);
@@ -1901,63 +1983,40 @@ __device__ __forceinline__ void lut_task_rows(const Hot& L, uint8_t* lds, uint32
   }
 }
 
-// Output-type dispatch of a full slot-table task (narrow or wide entries;
-// four tiles, or two with NCH = 1).  Returns false for the combinations the
-// steady state does not cover (they take the generic loop).
-template <int B, bool WIDE, bool DOT = false, int NCH = 2>
+// Output-type dispatch of a full four-tile slot-table task (narrow or wide
+// entries).  Returns false for the combinations the steady state does not
+// cover (they take the generic loop).
+template <int B, bool WIDE, bool DOT = false>
 __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
                                              uint32_t t0, int32_t* status) {
   if constexpr (DOT) {
-    if (NCH == 1 && L.cvec < L.V) return false;   // the generic loop adds vector by vector
     // two chains hold the sums of at most four rows of X in registers
-    if (NCH == 2 && L.m > 4) return false;
-    lut_task_rows<B, kOutDotI8, false, WIDE, NCH>(L, lds, ring_area, t0, status);
+    if (L.m > 4) return false;
+    lut_task_rows<B, kOutDotI8, false, WIDE>(L, lds, ring_area, t0, status);
     return true;
   }
-  if constexpr (NCH == 1) {
-    // the output types small layers are decoded to; the rest take the generic loop
-    switch (L.out_dtype) {
-      case EP_BF16:
-        if (L.saturate) lut_task_rows<B, EP_BF16, true, WIDE, 1>(L, lds, ring_area, t0, status);
-        else lut_task_rows<B, EP_BF16, false, WIDE, 1>(L, lds, ring_area, t0, status);
-        return true;
-      case EP_FP16:
-        if (L.saturate) lut_task_rows<B, EP_FP16, true, WIDE, 1>(L, lds, ring_area, t0, status);
-        else lut_task_rows<B, EP_FP16, false, WIDE, 1>(L, lds, ring_area, t0, status);
-        return true;
-      case EP_FP8_E4M3:
-        if (L.saturate) lut_task_rows<B, EP_FP8_E4M3, true, WIDE, 1>(L, lds, ring_area, t0, status);
-        else lut_task_rows<B, EP_FP8_E4M3, false, WIDE, 1>(L, lds, ring_area, t0, status);
-        return true;
-      case EP_INT8: lut_task_rows<B, EP_INT8, false, WIDE, 1>(L, lds, ring_area, t0, status); return true;
-      default: return false;
-    }
-  } else {
-    switch (L.out_dtype) {
-      case EP_BF16:
-        if (L.saturate) lut_task_rows<B, EP_BF16, true, WIDE, NCH>(L, lds, ring_area, t0, status);
-        else lut_task_rows<B, EP_BF16, false, WIDE, NCH>(L, lds, ring_area, t0, status);
-        return true;
-      case EP_FP16:
-        if (L.saturate) lut_task_rows<B, EP_FP16, true, WIDE, NCH>(L, lds, ring_area, t0, status);
-        else lut_task_rows<B, EP_FP16, false, WIDE, NCH>(L, lds, ring_area, t0, status);
-        return true;
-      case EP_FP8_E4M3:
-        if (L.saturate) lut_task_rows<B, EP_FP8_E4M3, true, WIDE, NCH>(L, lds, ring_area, t0, status);
-        else lut_task_rows<B, EP_FP8_E4M3, false, WIDE, NCH>(L, lds, ring_area, t0, status);
-        return true;
-      case EP_FP8_E5M2:
-        if (L.saturate) lut_task_rows<B, EP_FP8_E5M2, true, WIDE, NCH>(L, lds, ring_area, t0, status);
-        else lut_task_rows<B, EP_FP8_E5M2, false, WIDE, NCH>(L, lds, ring_area, t0, status);
-        return true;
-      case EP_INT8: lut_task_rows<B, EP_INT8, false, WIDE, NCH>(L, lds, ring_area, t0, status); return true;
-      case EP_UINT8: lut_task_rows<B, EP_UINT8, false, WIDE, NCH>(L, lds, ring_area, t0, status); return true;
-      case EP_FP32: lut_task_rows<B, EP_FP32, false, WIDE, NCH>(L, lds, ring_area, t0, status); return true;
-      case EP_COORD2_I32:
-        lut_task_rows<B, EP_COORD2_I32, false, WIDE, NCH>(L, lds, ring_area, t0, status);
-        return true;
-      default: return false;
-    }
+  switch (L.out_dtype) {
+    case EP_BF16:
+      if (L.saturate) lut_task_rows<B, EP_BF16, true, WIDE>(L, lds, ring_area, t0, status);
+      else lut_task_rows<B, EP_BF16, false, WIDE>(L, lds, ring_area, t0, status);
+      return true;
+    case EP_FP16:
+      if (L.saturate) lut_task_rows<B, EP_FP16, true, WIDE>(L, lds, ring_area, t0, status);
+      else lut_task_rows<B, EP_FP16, false, WIDE>(L, lds, ring_area, t0, status);
+      return true;
+    case EP_FP8_E4M3:
+      if (L.saturate) lut_task_rows<B, EP_FP8_E4M3, true, WIDE>(L, lds, ring_area, t0, status);
+      else lut_task_rows<B, EP_FP8_E4M3, false, WIDE>(L, lds, ring_area, t0, status);
+      return true;
+    case EP_FP8_E5M2:
+      if (L.saturate) lut_task_rows<B, EP_FP8_E5M2, true, WIDE>(L, lds, ring_area, t0, status);
+      else lut_task_rows<B, EP_FP8_E5M2, false, WIDE>(L, lds, ring_area, t0, status);
+      return true;
+    case EP_INT8: lut_task_rows<B, EP_INT8, false, WIDE>(L, lds, ring_area, t0, status); return true;
+    case EP_UINT8: lut_task_rows<B, EP_UINT8, false, WIDE>(L, lds, ring_area, t0, status); return true;
+    case EP_FP32: lut_task_rows<B, EP_FP32, false, WIDE>(L, lds, ring_area, t0, status); return true;
+    case EP_COORD2_I32: lut_task_rows<B, EP_COORD2_I32, false, WIDE>(L, lds, ring_area, t0, status); return true;
+    default: return false;
   }
 }
 
@@ -2109,12 +2168,19 @@ __device__ __forceinline__ void task_b(const Hot& L, const uint32_t* tab, uint8_
   const uint32_t nvec = L.rows * L.cvec;
   if constexpr (SMALL && (PATH == kPathLut || PATH == kPathWide) && B == 11) {
     if (L.tpt == 2) {
-      // two-tile tasks, one chain per wave (the fused product needs whole rounds)
+      // two-tile tasks, one chain per wave
       const uint32_t t0 = L.tile_begin + 2 * task;
       const bool whole = t0 + 2 <= L.tile_end && (uint64_t)(t0 + 2) * L.V <= nvec;
-      if (whole && L.V >= 32 && (!DOT || L.V % 32 == 0) && L.pay_bytes < kFastOob &&
-          lut_task_any<B, PATH == kPathWide, DOT, 1>(L, lb, ring_area, t0, status))
-        return;
+      constexpr bool WIDE = PATH == kPathWide;
+      if (L.pay_bytes < kFastOob) {
+        if constexpr (!DOT) {
+          lut_task1_any<B, WIDE>(L, lb, ring_area, t0, status);
+          return;
+        } else if (whole && L.V % 32 == 0 && L.cvec >= L.V) {
+          lut_task1<B, WIDE, kOutDotI8, true, kDotMaxTokens>(L, lb, ring_area, t0, status);
+          return;
+        }
+      }
       if (whole && L.V % 32 == 0) decode_task<PATH, B, 1, true, DOT>(L, tab, lb, ring_area, task, status);
       else decode_task<PATH, B, 1, false, DOT>(L, tab, lb, ring_area, task, status);
       return;
