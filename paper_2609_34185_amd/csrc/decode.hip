@@ -51,13 +51,17 @@ uint32_t lds_bytes(uint32_t path, const ep_tensor_info& I) {
   return search_layout(I.prob_bits, I.sum_alphabet).total + kRingBytes;
 }
 
-float dtype_max(int dt) {
+// Whether the weights need a clamp before the conversion to the output type.
+// The conversions to FP16 and FP8 saturate by themselves for finite FP32
+// inputs (saturate_conversions), so only weights that may be infinite in FP32
+// (ep_blob_info caps its bound at 3e38) need one; BF16's range ends below FP32's.
+bool needs_clamp(int dt, float max_abs_weight) {
   switch (dt) {
-    case EP_BF16: return 3.38953139e38f;
-    case EP_FP16: return 65504.0f;
-    case EP_FP8_E4M3: return 448.0f;
-    case EP_FP8_E5M2: return 57344.0f;
-    default: return 3.4e38f;
+    case EP_BF16: return max_abs_weight >= 3.38953139e38f;
+    case EP_FP16:
+    case EP_FP8_E4M3:
+    case EP_FP8_E5M2: return max_abs_weight >= 3.0e38f;
+    default: return false;   // FP32 as it is; the integer types clamp in their conversion
   }
 }
 
@@ -100,7 +104,7 @@ int fill_layer(const ep_tensor_info& I, const void* d_blob, int out_dtype, void*
   D.tpt = kTilesPerTask;
   D.n_tasks = (t1 - t0 + kTilesPerTask - 1) / kTilesPerTask;
   D.out_dtype = (uint32_t)out_dtype;
-  D.saturate = I.max_abs_weight >= dtype_max(out_dtype) ? 1u : 0u;
+  D.saturate = needs_clamp(out_dtype, I.max_abs_weight) ? 1u : 0u;
   D.coset_f0 = I.coset_f0;
   D.coset_f1 = I.coset_f1;
   D.sum_A = I.sum_alphabet;

@@ -163,6 +163,7 @@ __global__ __launch_bounds__(kThreads) void decode_gemm_kernel(const GemmLaunch 
   const GemmLaunch& A = launch;
 #endif
   extern __shared__ uint32_t lds[];
+  saturate_conversions();
   const LayerDev& L = A.L;
   const GemmArgs& g = A.g;
   if (L.tables) load_tables<PATH>(L, lds);   // prepared by ep_decode_gemm_prepare
