@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kThreads) void decode_gemm_kernel(const GemmLaunch 
     H.out = uni_ptr(reinterpret_cast<void*>(reinterpret_cast<intptr_t>(slab) - (intptr_t)shift));
     const uint32_t tasks = (H.tile_end - H.tile_begin + kTilesPerTask - 1) / kTilesPerTask;
     for (uint32_t task = wave_id(); task < tasks; task += kWavesPerGroup)
-      dispatch_task<PATH, false>(H, lds, lb, ring_area, task, status);
+      dispatch_task<PATH, false, false, false>(H, lds, lb, ring_area, task, status);
     __syncthreads();   // the block's rows are in the slab
     block_product<BF, WIDE>(L, g, slab, b);
     __syncthreads();   // every wave is done with the slab

@@ -100,6 +100,7 @@ struct LayerDev {
   uint32_t path;                  // decode path of the layer (DecodePath)
   uint32_t tpt;                   // tiles per task: 4 (two chains per wave) or 2 (one chain)
   uint32_t g_bits, g_meta;        // global-table path: log2 G, byte offset of its metadata
+  uint32_t stream;                // four-tile steady state: payload and output bypass the caches
   const uint8_t* tables;          // prepared stacks: the layer's decode tables as built in LDS
                                   // (ring_offset bytes), copied in instead of rebuilt; or null
 };
@@ -121,6 +122,7 @@ struct Hot {
   uint32_t g_bits, g_meta;        // global-table path: log2 G, u32 index of the metadata
   uint32_t tab_bytes;             // end of the tables section (bounds of their loads)
   uint32_t tpt;                   // tiles per task (LayerDev::tpt)
+  uint32_t stream;                // LayerDev::stream
 };
 
 __device__ __forceinline__ uint32_t uni(uint32_t v) {
@@ -171,6 +173,7 @@ __device__ __forceinline__ Hot make_hot(const LayerDev& L) {
   H.g_meta = uni(L.g_meta / 4);
   H.tab_bytes = uni((uint32_t)L.off_sigma);
   H.tpt = uni(L.tpt);
+  H.stream = uni(L.stream);
   return H;
 }
 
@@ -874,11 +877,24 @@ struct FastChain {     // wave-uniform, in payload words
   uint32_t EA, EB;     // end of each tile's stream, same origin as CA / CB
 };
 
+// Payload of the four-tile steady state (bounded buffer loads), streaming or
+// not (LayerDev::stream): 8 and 16 bytes a lane.  A template argument: a branch
+// at the loads makes the compiler wait for them where the two sides meet.
+template <bool STREAM>
+__device__ __forceinline__ u32x2 payload_b64(__amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, STREAM ? 2 : 0);
+}
+template <bool STREAM>
+__device__ __forceinline__ u32x4 payload_b128(__amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, STREAM ? 2 : 0);
+}
+
 // Commit the staged block of half A (lanes 0-31, registers pendA) if its
 // margin is below `limit`, and request its next block; likewise half B (lanes
 // 32-63, pendB).  The positions stay wave-uniform (scalar registers); only the
 // commit and the request are per lane.  Separate staging registers per half
 // keep a commit of one half from waiting for the other half's request.
+template <bool STREAM>
 __device__ __forceinline__ void fast_stage(FastChain& F, u32x2& pendA, u32x2& pendB, uint8_t* lds,
                                            uint32_t vrb8,
                                            uint32_t vl8, __amdgpu_buffer_rsrc_t rsrc,
@@ -888,14 +904,12 @@ __device__ __forceinline__ void fast_stage(FastChain& F, u32x2& pendA, u32x2& pe
     if (cA && half == 0) {
       *reinterpret_cast<u32x2*>(lds + vrb8 + 2 * (F.QA & (kFastRingWords - 1))) = pendA;
       const uint32_t a = F.QA + kFastBlockWords;
-      pendA = __builtin_amdgcn_raw_buffer_load_b64(
-          rsrc, uni(a < F.EA ? 2 * (F.CA + a) : kFastOob) + vl8, 0, 0);
+      pendA = payload_b64<STREAM>(rsrc, uni(a < F.EA ? 2 * (F.CA + a) : kFastOob) + vl8);
     }
     if (cB && half == 1) {
       *reinterpret_cast<u32x2*>(lds + vrb8 + 2 * (F.QB & (kFastRingWords - 1))) = pendB;
       const uint32_t a = F.QB + kFastBlockWords;
-      pendB = __builtin_amdgcn_raw_buffer_load_b64(
-          rsrc, uni(a < F.EB ? 2 * (F.CB + a) : kFastOob) + vl8, 0, 0);
+      pendB = payload_b64<STREAM>(rsrc, uni(a < F.EB ? 2 * (F.CB + a) : kFastOob) + vl8);
     }
     F.QA = uni(F.QA + (cA ? kFastBlockWords : 0u));
     F.QB = uni(F.QB + (cB ? kFastBlockWords : 0u));
@@ -962,6 +976,7 @@ __device__ __forceinline__ uint32_t smin(uint32_t a, uint32_t b) {
 // smallest of the four margins skips the per-half work when no half needs it
 // (the common case: at typical rates a half consumes well under a block per
 // round).
+template <bool STREAM = false>
 __device__ __forceinline__ void fast_stage_both(FastChain& F0, FastChain& F1, u32x2& pendA0,
                                                 u32x2& pendB0, u32x2& pendA1, u32x2& pendB1,
                                                 uint8_t* lds, uint32_t vrb08, uint32_t vrb18,
@@ -970,11 +985,12 @@ __device__ __forceinline__ void fast_stage_both(FastChain& F0, FastChain& F1, u3
   const uint32_t m = smin(smin(F0.QA - F0.OA, F0.QB - F0.OA - F0.D),
                           smin(F1.QA - F1.OA, F1.QB - F1.OA - F1.D));
   if (__builtin_expect(m < limit, 0)) {
-    fast_stage(F0, pendA0, pendB0, lds, vrb08, vl8, rsrc, half, limit);
-    fast_stage(F1, pendA1, pendB1, lds, vrb18, vl8, rsrc, half, limit);
+    fast_stage<STREAM>(F0, pendA0, pendB0, lds, vrb08, vl8, rsrc, half, limit);
+    fast_stage<STREAM>(F1, pendA1, pendB1, lds, vrb18, vl8, rsrc, half, limit);
   }
 }
 
+template <bool STREAM = false>
 __device__ __forceinline__ u32x4 fast_start(FastChain& F, u32x2& pend, __amdgpu_buffer_rsrc_t rsrc,
                                             uint32_t half, uint32_t l, uint32_t pA0, uint32_t pA1,
                                             uint32_t pB0, uint32_t pB1) {
@@ -986,9 +1002,8 @@ __device__ __forceinline__ u32x4 fast_start(FastChain& F, u32x2& pend, __amdgpu_
   F.EA = pA1 - F.CA;
   F.EB = pB1 - F.CB;
   const uint32_t c = half ? F.CB : F.CA, e = half ? F.EB : F.EA;
-  const u32x4 first = __builtin_amdgcn_raw_buffer_load_b128(rsrc, 2 * c + 16 * l, 0, 0);
-  pend = __builtin_amdgcn_raw_buffer_load_b64(
-      rsrc, (kFastRingWords < e ? 2 * (c + kFastRingWords) : kFastOob) + 8 * l, 0, 0);
+  const u32x4 first = payload_b128<STREAM>(rsrc, 2 * c + 16 * l);
+  pend = payload_b64<STREAM>(rsrc, (kFastRingWords < e ? 2 * (c + kFastRingWords) : kFastOob) + 8 * l);
   return first;
 }
 
@@ -1505,17 +1520,21 @@ __device__ __forceinline__ void q_take(QAcc& a, uint32_t e, float y, uint32_t c)
   }
 }
 
-// Store the packed vector at base + off.
-template <int DT>
+// Store the packed vector at base + off, streaming or not.
+template <int DT, bool STREAM>
 __device__ __forceinline__ void q_put(EP_GLOBAL uint8_t* base, uint32_t off, const QAcc& a) {
+  auto put = [&](auto* p, auto v) {
+    if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  };
   if constexpr (DT == EP_BF16 || DT == EP_FP16) {
-    *reinterpret_cast<EP_GLOBAL u32x4*>(base + off) = u32x4{a.w[0], a.w[1], a.w[2], a.w[3]};
+    put(reinterpret_cast<EP_GLOBAL u32x4*>(base + off), u32x4{a.w[0], a.w[1], a.w[2], a.w[3]});
   } else if constexpr (DT == EP_FP8_E4M3 || DT == EP_FP8_E5M2 || DT == EP_INT8 || DT == EP_UINT8) {
-    *reinterpret_cast<EP_GLOBAL u32x2*>(base + off) = u32x2{a.w[0], a.w[1]};
+    put(reinterpret_cast<EP_GLOBAL u32x2*>(base + off), u32x2{a.w[0], a.w[1]});
   } else {
     EP_GLOBAL u32x4* o = reinterpret_cast<EP_GLOBAL u32x4*>(base + off);
-    o[0] = u32x4{a.w[0], a.w[1], a.w[2], a.w[3]};
-    o[1] = u32x4{a.w[4], a.w[5], a.w[6], a.w[7]};
+    put(o, u32x4{a.w[0], a.w[1], a.w[2], a.w[3]});
+    put(o + 1, u32x4{a.w[4], a.w[5], a.w[6], a.w[7]});
   }
 }
 
@@ -1555,7 +1574,7 @@ __device__ __forceinline__ int32_t half_sum(int32_t v) {
 // used once the vector's first four weights are known (after field 4), when
 // columns 4-7 are requested, used at the end of the round.
 // Without TWO every vector is added to Y on its own.
-template <int B, int DT, bool SAT, bool TWO, bool WIDE, int MT = 1>
+template <int B, int DT, bool SAT, bool TWO, bool WIDE, int MT = 1, bool STREAM = false>
 __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ring_area, uint32_t t0,
                                          int32_t* status) {
   const uint32_t lane = threadIdx.x & 63, wave = wave_id();
@@ -1615,8 +1634,8 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
   u32x2 pend0, pend1, pendB0, pendB1;
 #pragma unroll
   for (int i = 0; i < 5; i++) o[i] = uni(o[i]);
-  const u32x4 fill0 = fast_start(F0, pend0, rsrc, half, l, o[0], o[1], o[1], o[2]);
-  const u32x4 fill1 = fast_start(F1, pend1, rsrc, half, l, o[2], o[3], o[3], o[4]);
+  const u32x4 fill0 = fast_start<STREAM>(F0, pend0, rsrc, half, l, o[0], o[1], o[1], o[2]);
+  const u32x4 fill1 = fast_start<STREAM>(F1, pend1, rsrc, half, l, o[2], o[3], o[3], o[4]);
   // One wait for everything requested so far, so that no load is in flight
   // when the loop starts (the loop's own waits then stay one round behind).
   __builtin_amdgcn_s_waitcnt(0);
@@ -1648,7 +1667,7 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
       xsave[1] = x[1];
     }
     // room for a block: margin <= ring - block
-    fast_stage_both(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half,
+    fast_stage_both<STREAM>(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half,
                     kFastRingWords - kFastBlockWords + 1);
     float sg[2], hc[2];
 #pragma unroll
@@ -1697,7 +1716,7 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
   q_take<DT, I, WIDE>(acc[0], e0, y0, cb[0] >> (B + 5));                                      \
   q_take<DT, I, WIDE>(acc[1], e1, y1, cb[1] >> (B + 5));
     EP_FIELD(1) EP_FIELD(2)
-    fast_stage_both(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
+    fast_stage_both<STREAM>(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
     EP_FIELD(3) EP_FIELD(4)
     if constexpr (ACC) {
 #pragma unroll
@@ -1710,7 +1729,7 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
       }
     }
     EP_FIELD(5)
-    fast_stage_both(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
+    fast_stage_both<STREAM>(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
     EP_FIELD(6) EP_FIELD(7) EP_FIELD(8)
 #undef EP_FIELD
 #undef EP_PIN
@@ -1728,8 +1747,8 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
       }
     } else {
       if (!PART || !pin) {
-        q_put<DT>(obase, voff[0], acc[0]);
-        q_put<DT>(obase, voff[1], acc[1]);
+        q_put<DT, STREAM>(obase, voff[0], acc[0]);
+        q_put<DT, STREAM>(obase, voff[1], acc[1]);
       }
       obase += 32 * VB;
     }
@@ -1975,7 +1994,7 @@ __device__ __forceinline__ void lut_task1_any(const Hot& L, uint8_t* lds, uint32
 }
 
 // Row-scale and sum variants of a full four-tile slot-table task.
-template <int B, int DT, bool SAT, bool WIDE>
+template <int B, int DT, bool SAT, bool WIDE, bool STREAM = false>
 __device__ __forceinline__ void lut_task_rows(const Hot& L, uint8_t* lds, uint32_t ring_area,
                                               uint32_t t0, int32_t* status) {
   if constexpr (DT == kOutDotI8) {
@@ -1990,15 +2009,18 @@ __device__ __forceinline__ void lut_task_rows(const Hot& L, uint8_t* lds, uint32
   } else {
     // a lane's vectors v, v + 32, ..., v + 32 (ceil(V / 32) - 1) lie in at most two rows when
     // C/8 is at least their span
-    if (L.cvec >= 32 * ((L.V - 1) / 32)) lut_task<B, DT, SAT, true, WIDE>(L, lds, ring_area, t0, status);
-    else lut_task<B, DT, SAT, false, WIDE>(L, lds, ring_area, t0, status);
+    if (L.cvec >= 32 * ((L.V - 1) / 32)) lut_task<B, DT, SAT, true, WIDE, 1, STREAM>(L, lds, ring_area, t0, status);
+    else lut_task<B, DT, SAT, false, WIDE, 1, STREAM>(L, lds, ring_area, t0, status);
   }
 }
 
 // Output-type dispatch of a full four-tile slot-table task (narrow or wide
-// entries).  Returns false for the combinations the steady state does not
-// cover (they take the generic loop).
-template <int B, bool WIDE, bool DOT = false>
+// entries).  STREAMS: the kernel may stream (the fused MFMA products, which
+// read their slab back, have no such instances).  Returns false for the
+// combinations the steady state does not cover (they take the generic loop).
+// The explicit clamp has instances only for the types whose conversion it may
+// be needed for, and neither it nor the rarer outputs have streaming ones.
+template <int B, bool WIDE, bool DOT = false, bool STREAMS = true>
 __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
                                              uint32_t t0, int32_t* status) {
   if constexpr (DOT) {
@@ -2006,29 +2028,37 @@ __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_
     if (L.m > 4) return false;
     lut_task_rows<B, kOutDotI8, false, WIDE>(L, lds, ring_area, t0, status);
     return true;
-  }
-  switch (L.out_dtype) {
-    case EP_BF16:
-      if (L.saturate) lut_task_rows<B, EP_BF16, true, WIDE>(L, lds, ring_area, t0, status);
-      else lut_task_rows<B, EP_BF16, false, WIDE>(L, lds, ring_area, t0, status);
-      return true;
-    case EP_FP16:
-      if (L.saturate) lut_task_rows<B, EP_FP16, true, WIDE>(L, lds, ring_area, t0, status);
-      else lut_task_rows<B, EP_FP16, false, WIDE>(L, lds, ring_area, t0, status);
-      return true;
-    case EP_FP8_E4M3:
-      if (L.saturate) lut_task_rows<B, EP_FP8_E4M3, true, WIDE>(L, lds, ring_area, t0, status);
-      else lut_task_rows<B, EP_FP8_E4M3, false, WIDE>(L, lds, ring_area, t0, status);
-      return true;
-    case EP_FP8_E5M2:
-      if (L.saturate) lut_task_rows<B, EP_FP8_E5M2, true, WIDE>(L, lds, ring_area, t0, status);
-      else lut_task_rows<B, EP_FP8_E5M2, false, WIDE>(L, lds, ring_area, t0, status);
-      return true;
-    case EP_INT8: lut_task_rows<B, EP_INT8, false, WIDE>(L, lds, ring_area, t0, status); return true;
-    case EP_UINT8: lut_task_rows<B, EP_UINT8, false, WIDE>(L, lds, ring_area, t0, status); return true;
-    case EP_FP32: lut_task_rows<B, EP_FP32, false, WIDE>(L, lds, ring_area, t0, status); return true;
-    case EP_COORD2_I32: lut_task_rows<B, EP_COORD2_I32, false, WIDE>(L, lds, ring_area, t0, status); return true;
-    default: return false;
+  } else {
+    auto plain = [&](auto dt) {
+      constexpr int DT = decltype(dt)::value;
+      if constexpr (STREAMS) {
+        if (L.stream) {
+          lut_task_rows<B, DT, false, WIDE, true>(L, lds, ring_area, t0, status);
+          return;
+        }
+      }
+      lut_task_rows<B, DT, false, WIDE>(L, lds, ring_area, t0, status);
+    };
+    switch (L.out_dtype) {
+      case EP_BF16: plain(std::integral_constant<int, EP_BF16>{}); return true;
+      case EP_FP16:
+        if (L.saturate) lut_task_rows<B, EP_FP16, true, WIDE>(L, lds, ring_area, t0, status);
+        else plain(std::integral_constant<int, EP_FP16>{});
+        return true;
+      case EP_FP8_E4M3:
+        if (L.saturate) lut_task_rows<B, EP_FP8_E4M3, true, WIDE>(L, lds, ring_area, t0, status);
+        else plain(std::integral_constant<int, EP_FP8_E4M3>{});
+        return true;
+      case EP_FP8_E5M2:
+        if (L.saturate) lut_task_rows<B, EP_FP8_E5M2, true, WIDE>(L, lds, ring_area, t0, status);
+        else lut_task_rows<B, EP_FP8_E5M2, false, WIDE>(L, lds, ring_area, t0, status);
+        return true;
+      case EP_INT8: plain(std::integral_constant<int, EP_INT8>{}); return true;
+      case EP_UINT8: lut_task_rows<B, EP_UINT8, false, WIDE>(L, lds, ring_area, t0, status); return true;
+      case EP_FP32: plain(std::integral_constant<int, EP_FP32>{}); return true;
+      case EP_COORD2_I32: lut_task_rows<B, EP_COORD2_I32, false, WIDE>(L, lds, ring_area, t0, status); return true;
+      default: return false;
+    }
   }
 }
 
@@ -2173,8 +2203,9 @@ constexpr uint32_t kTilesPerTask = 4;
 static_assert(kChains == 2, "the generic loop and the search steady state advance two chains");
 static_assert(kTilesPerTask == 2 * kChains, "task granularity: one four-tile pass");
 
-// SMALL: the kernel may run two-tile tasks (see use_small_tasks).
-template <int PATH, int B, bool DOT, bool SMALL>
+// SMALL: the kernel may run two-tile tasks (see use_small_tasks).  STREAMS: it
+// may stream (see lut_task_any).
+template <int PATH, int B, bool DOT, bool SMALL, bool STREAMS>
 __device__ __forceinline__ void task_b(const Hot& L, const uint32_t* tab, uint8_t* lb,
                                        uint32_t ring_area, uint32_t task, int32_t* status) {
   const uint32_t nvec = L.rows * L.cvec;
@@ -2207,7 +2238,7 @@ __device__ __forceinline__ void task_b(const Hot& L, const uint32_t* tab, uint8_
   const bool lut_ok = whole && (full || (!DOT && L.V >= 32));
   if (L.pay_bytes < kFastOob && ((PATH == kPathSearch && full) || (B == 11 && lut_ok))) {
     if constexpr (PATH != kPathSearch && B == 11) {
-      if (lut_task_any<B, PATH == kPathWide, DOT>(L, lb, ring_area, t0, status)) return;
+      if (lut_task_any<B, PATH == kPathWide, DOT, STREAMS>(L, lb, ring_area, t0, status)) return;
     } else if constexpr (PATH == kPathSearch) {
       if (decode_task_fast_any<PATH, B, DOT>(L, lb, ring_area, task, status)) return;
     }
@@ -2217,13 +2248,13 @@ __device__ __forceinline__ void task_b(const Hot& L, const uint32_t* tab, uint8_
   else decode_task<PATH, B, kChains, false, DOT>(L, tab, lb, ring_area, task, status);
 }
 
-template <int PATH, bool DOT, bool SMALL = false>
+template <int PATH, bool DOT, bool SMALL = false, bool STREAMS = true>
 __device__ __forceinline__ void dispatch_task(const Hot& L, const uint32_t* tab, uint8_t* lb,
                                               uint32_t ring_area, uint32_t task, int32_t* status) {
-  if (PATH == kPathSearch || PATH == kPathGlobal) task_b<PATH, 0, DOT, SMALL>(L, tab, lb, ring_area, task, status);
-  else if (L.b == 11) task_b<PATH, 11, DOT, SMALL>(L, tab, lb, ring_area, task, status);
-  else if (L.b == 10) task_b<PATH, 10, DOT, SMALL>(L, tab, lb, ring_area, task, status);
-  else task_b<PATH, 9, DOT, SMALL>(L, tab, lb, ring_area, task, status);
+  if (PATH == kPathSearch || PATH == kPathGlobal) task_b<PATH, 0, DOT, SMALL, STREAMS>(L, tab, lb, ring_area, task, status);
+  else if (L.b == 11) task_b<PATH, 11, DOT, SMALL, STREAMS>(L, tab, lb, ring_area, task, status);
+  else if (L.b == 10) task_b<PATH, 10, DOT, SMALL, STREAMS>(L, tab, lb, ring_area, task, status);
+  else task_b<PATH, 9, DOT, SMALL, STREAMS>(L, tab, lb, ring_area, task, status);
 }
 
 // Decode global tasks [t_begin, t_end) of a layer list: per layer segment the

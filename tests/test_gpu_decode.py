@@ -588,3 +588,32 @@ def test_config4_full_stack_sampled_tiles(E, oracle):
             got = flat[a:b].cpu().numpy().view(np.uint16)
             assert np.array_equal(got, ref.reshape(-1)[a:b]), (name, t)
     say("  sampled tiles of all 180 layers equal the oracle")
+
+
+@pytest.mark.parametrize("name,container", [("FP32", 0), ("FP16", 0), ("FP8", 1), ("INT8", 2)])
+def test_launch_larger_than_the_last_level_cache(E, oracle, name, container):
+    """A list of layers that moves more than 256 MiB takes the streaming stores and loads: one
+    blob decoded into as many outputs as that needs, each equal to the oracle's decode.  BF16
+    and the full-size FP8 set are streamed by the configuration tests."""
+    w = W.draw_tensor(np.random.default_rng(11), 1500, 2048, **W.CFG3)
+    blob, _ = oracle.encode(w, 6.0 if container == 2 else 4.0, container=container)
+    info = E.blob_info(blob)
+    ecode, ocode = codes(E, oracle, name)
+    ref, ref_dq = oracle.decode(blob, ocode)
+    d_blob = E.to_device(blob)
+    n = (256 << 20) // (ref.nbytes + 2 * info.payload_words) + 1
+    out = torch.zeros((n, 1500, 2048), dtype=E.torch_dtype(ecode), device="cuda")
+    dq = torch.zeros((n, 1500), dtype=torch.float32, device="cuda")
+    layers = [(info, d_blob.data_ptr(), out[i].data_ptr(), dq[i].data_ptr(), ecode) for i in range(n)]
+    ws = torch.zeros(E.decode_layers_workspace(n), dtype=torch.uint8, device="cuda")
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    say(f"  {n} layers -> {name}")
+    E.decode_layers(layers, ws.data_ptr(), ws.numel(), st.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    assert np.array_equal(gpu_bits(out[0]), ref)
+    bits = out.view(torch.int32 if out.element_size() == 4 else torch.int16 if out.element_size() == 2
+                    else torch.uint8)
+    assert all(bool((bits[i] == bits[0]).all()) for i in range(1, n))
+    if container:
+        assert all(np.array_equal(dq[i].cpu().numpy(), ref_dq) for i in range(n))
