@@ -45,10 +45,14 @@ DeviceProps device_props() {
   return cache[dev];
 }
 
+bool may_compact(const ep_tensor_info& I) {
+  return compact_possible(I.prob_bits, I.sum_alphabet, I.coord2_min, I.coord2_max);
+}
+
 uint32_t lds_bytes(uint32_t path, const ep_tensor_info& I) {
   if (path == kPathGlobal) return global_layout(I.table_A).total + kRingBytes;
   if (path != kPathSearch) return (64u << I.prob_bits) + kRingBytes;
-  return search_layout(I.prob_bits, I.sum_alphabet).total + kRingBytes;
+  return search_area(I.prob_bits, I.sum_alphabet, may_compact(I)) + kRingBytes;
 }
 
 // Whether the weights need a clamp before the conversion to the output type.
@@ -108,6 +112,7 @@ int fill_layer(const ep_tensor_info& I, const void* d_blob, int out_dtype, void*
   D.coset_f0 = I.coset_f0;
   D.coset_f1 = I.coset_f1;
   D.sum_A = I.sum_alphabet;
+  D.compact = I.path == kPathSearch && may_compact(I) ? 1u : 0u;
   const uint64_t pay = (2ull * I.payload_words + 3) / 4 * 4;
   if (pay > 0xFFFFFFF0ull) return fail(EP_ERR_UNSUPPORTED, "decode: payload section above 4 GiB");
   D.pay_bytes = (uint32_t)pay;
@@ -249,9 +254,9 @@ int launch_layers(uint32_t path, const std::vector<LayerDev>& D, uint32_t total,
 }
 
 // A launch of fewer four-tile tasks than this runs two-tile tasks (one chain
-// per wave) when every layer takes the same slot-table path at b = 11: twice
-// as many waves, each issuing half the instructions per symbol (see
-// field_step1).  The environment variable EP_SMALL_TASK_LIMIT overrides the
+// per wave) when every layer takes the same slot-table path at b = 11, or the
+// search path in its compact form: twice as many waves, each issuing half the
+// instructions per symbol (see field_step1).  The environment variable EP_SMALL_TASK_LIMIT overrides the
 // limit (0: always four-tile tasks).
 constexpr uint32_t kSmallLaunchTasks = 2048;
 
@@ -266,8 +271,9 @@ uint32_t small_task_limit() {
 void use_small_tasks(std::vector<LayerDev>& D, uint32_t& total) {
   if (total == 0 || total >= small_task_limit()) return;
   for (const LayerDev& d : D)
-    if ((d.path != kPathLut && d.path != kPathWide) || d.path != D[0].path || d.out_dtype == kOutDotI8 ||
-        d.b != 11)
+    if (d.path != D[0].path || d.out_dtype == kOutDotI8 ||
+        !(d.path == kPathSearch ? d.compact && compact_certain(d.sum_A)
+                                : (d.path == kPathLut || d.path == kPathWide) && d.b == 11))
       return;
   uint32_t tasks = 0;
   for (LayerDev& d : D) {

@@ -183,6 +183,7 @@ __global__ __launch_bounds__(kThreads) void decode_gemm_kernel(const GemmLaunch 
     const uint64_t v_end_b = (uint64_t)(b + 1) * RB * L.cvec;
     const uint64_t v_end = v_end_b < nvec ? v_end_b : nvec;
     Hot H = make_hot(L);
+    set_form<PATH>(H, L, lds);
     const uint32_t t_end = (uint32_t)((v_end + L.V - 1) / L.V);
     H.tile_begin = uni((uint32_t)(v_first / L.V) / kTilesPerTask * kTilesPerTask);
     H.tile_end = uni(min(L.tile_end, (t_end + kTilesPerTask - 1) / kTilesPerTask * kTilesPerTask));

@@ -28,8 +28,9 @@
 //   kPathWide   the same table with wide entries for larger coordinates:
 //               f - 1 (bits 0-10), u - F (bits 11-21) and z as a signed
 //               10-bit field (bits 22-31); one more add per symbol;
-//   kPathSearch per-symbol cumulative table (F | f << 16) searched with a
-//               fixed-trip binary search -- any b, alphabets up to the LDS size;
+//   kPathSearch buckets of slots over the symbols that occur (compact form, two
+//               dependent LDS reads a symbol), or over cumulative values with a
+//               binary search -- any b, alphabets up to the LDS size;
 //   kPathGlobal every G-th cumulative value in LDS, the frequencies themselves
 //               read from the blob in global memory -- any valid table.
 #pragma once
@@ -100,6 +101,7 @@ struct LayerDev {
   uint32_t path;                  // decode path of the layer (DecodePath)
   uint32_t tpt;                   // tiles per task: 4 (two chains per wave) or 2 (one chain)
   uint32_t g_bits, g_meta;        // global-table path: log2 G, byte offset of its metadata
+  uint32_t compact;               // search path: the compact form may be tried
   uint32_t stream;                // four-tile steady state: payload and output bypass the caches
   const uint8_t* tables;          // prepared stacks: the layer's decode tables as built in LDS
                                   // (ring_offset bytes), copied in instead of rebuilt; or null
@@ -123,6 +125,8 @@ struct Hot {
   uint32_t tab_bytes;             // end of the tables section (bounds of their loads)
   uint32_t tpt;                   // tiles per task (LayerDev::tpt)
   uint32_t stream;                // LayerDev::stream
+  uint32_t form;                  // search path: 0 cumulative, else the compact form's kind (kCompact*)
+  uint32_t bk, ck, csh;           // compact form: byte offset of the buckets, k, max(b - k, 0)
 };
 
 __device__ __forceinline__ uint32_t uni(uint32_t v) {
@@ -174,6 +178,8 @@ __device__ __forceinline__ Hot make_hot(const LayerDev& L) {
   H.tab_bytes = uni((uint32_t)L.off_sigma);
   H.tpt = uni(L.tpt);
   H.stream = uni(L.stream);
+  H.form = 0;
+  H.bk = H.ck = H.csh = 0;
   return H;
 }
 
@@ -649,9 +655,52 @@ __device__ __forceinline__ void refill(uint32_t& x, bool act, uint64_t act_mask,
   if (Bh.S2 >= Bh.T2) commit_half<NC>(lds, Bh, pend, rsrc, half == 1, l);
 }
 
+// The compact search form's kinds: every bucket one slot (b <= 11); two slots
+// (b = 12, k = 11: the symbol is the bucket's or the next one); any.
+constexpr int kCompactSlot = 1, kCompactPair = 2, kCompactAny = 3;
+
+// Entry e0 of the symbol of state x in field FIELD's table and the entry e1
+// after it (F | z << 16 each; f is the difference of the two F).  cbk: byte
+// offset of the buckets of the coset's first table.  The entries of a table end
+// with F = 2^b > u, and buckets of tables without symbols hold that end, so the
+// index stays inside the entries for any x.
+template <int KIND>
+__device__ __forceinline__ void compact_entries(const Hot& L, const uint32_t* lds, int field,
+                                                uint32_t cbk, uint32_t x, uint32_t& e0, uint32_t& e1) {
+  const uint8_t* const lb = reinterpret_cast<const uint8_t*>(lds);
+  const uint32_t u = x & ((1u << L.b) - 1);
+  uint32_t a;
+  if constexpr (KIND == kCompactSlot) a = cbk + 2 * u + ((uint32_t)(field - 1) << (kCompactBits + 1));
+  else if constexpr (KIND == kCompactPair) a = cbk + (u & ~1u) + ((uint32_t)(field - 1) << (kCompactBits + 1));
+  else a = cbk + 2 * (u >> L.csh) + ((uint32_t)(field - 1) << (L.ck + 1));
+  uint32_t i = *reinterpret_cast<const uint16_t*>(lb + a);
+  e0 = lds[i];
+  e1 = lds[i + 1];
+  if constexpr (KIND != kCompactSlot) {
+    const uint32_t e2 = lds[i + 2];
+    const bool next = u >= (e1 & 0xFFFFu);
+    e0 = next ? e1 : e0;
+    e1 = next ? e2 : e1;
+    if constexpr (KIND == kCompactAny) {
+      if (L.csh > 1) {   // more than two slots a bucket: step on while any lane has to
+        i += next ? 2 : 1;   // index of e1
+        for (uint32_t k = 2; k < (1u << L.csh); k++) {
+          const bool more = u >= (e1 & 0xFFFFu);
+          if (!__any(more)) break;
+          if (more) {
+            e0 = e1;
+            e1 = lds[++i];
+          }
+        }
+      }
+    }
+  }
+}
+
 // One field symbol.  Slot-table path: entry = lut[(8c + i - 1) * 2^B + u]; the
 // coset part cb = 8c * 2^B is per lane, the field part a constant offset.
-template <int PATH, int B>
+// CUMULATIVE: the search tables are known to be in that form.
+template <int PATH, int B, bool CUMULATIVE = false>
 __device__ __forceinline__ void decode_field(const Hot& L, const uint32_t* lds, int field,
                                              uint32_t cb, uint32_t c, uint32_t& x, int32_t& dval) {
   if (PATH == kPathLut) {
@@ -705,6 +754,13 @@ __device__ __forceinline__ void decode_field(const Hot& L, const uint32_t* lds, 
     }
     x = __umul24(f, x >> L.b) + u - F;
     dval = doubled_value((int32_t)s + (int32_t)lds[L.g_meta + 16 + t], field, c);
+  } else if (!CUMULATIVE && L.form) {
+    // compact form, any kind (the steady states have their own instances)
+    uint32_t e0, e1;
+    compact_entries<kCompactAny>(L, lds, field, L.bk + (c << (L.ck + 4)), x, e0, e1);
+    const uint32_t F = e0 & 0xFFFFu;
+    x = __umul24((e1 & 0xFFFFu) - F, x >> L.b) + (x & ((1u << L.b) - 1)) - F;
+    dval = 2 * ((int32_t)e0 >> 16) + (int32_t)c;
   } else {
     // Bucketed search: the bucket j of u (its top k bits) bounds the symbol to
     // [bk[j], bk[j + 1]]; a binary search on the u16 cumulative table narrows
@@ -956,7 +1012,7 @@ __device__ __forceinline__ void field_step_search(const Hot& L, const uint32_t* 
                                                   FastChain& F1, const uint8_t* lds, uint32_t vrb0,
                                                   uint32_t vrb1, uint32_t vH) {
 #pragma unroll
-  for (int j = 0; j < 2; j++) decode_field<kPathSearch, 0>(L, tab, FIELD, 0, c[j], x[j], d[j][FIELD]);
+  for (int j = 0; j < 2; j++) decode_field<kPathSearch, 0, true>(L, tab, FIELD, 0, c[j], x[j], d[j][FIELD]);
   refill_staged(x[0], F0.OA, F0.D, lds, vrb0, vH);
   refill_staged(x[1], F1.OA, F1.D, lds, vrb1, vH);
 }
@@ -1007,9 +1063,9 @@ __device__ __forceinline__ u32x4 fast_start(FastChain& F, u32x2& pend, __amdgpu_
   return first;
 }
 
-// The steady-state task of the search path: four full tiles (two chains),
-// output type DT.
-template <int PATH, int B, int DT, bool SAT>
+// The steady-state task of the search path's cumulative form: four full tiles
+// (two chains), stored in the layer's output type or multiplied into X (DOT).
+template <bool DOT>
 __device__ __forceinline__ void decode_task_fast(const Hot& L, uint8_t* lds, uint32_t ring_area,
                                                  uint32_t task, int32_t* status) {
   const uint32_t* tab = reinterpret_cast<const uint32_t*>(lds);
@@ -1088,8 +1144,7 @@ __device__ __forceinline__ void decode_task_fast(const Hot& L, uint8_t* lds, uin
         acc += d[j][i];
       }
       p2[7] = d[j][8] | (acc & 2);
-      if constexpr (DT == kOutDotI8) dot_vec(L, v0[j] + l + 32 * k, p2, 0.5f * sg[j]);
-      else store_vec<DT, SAT>(L.out, v0[j] + l + 32 * k, p2, 0.5f * sg[j]);
+      store_vector<DOT>(L, v0[j] + l + 32 * k, p2, 0.5f * sg[j]);
       // next vector of this lane: 32 vectors further
       if (wide) {
         col[j] += 32;
@@ -1314,6 +1369,69 @@ __device__ __forceinline__ void coset_step2(uint32_t& x0, uint32_t& x1, uint32_t
       : EP_STEP_CLOBBERS);
 }
 
+// ---- compact search form: coset and field steps of two chains ---------------------
+// The table reads are plain code (two dependent LDS reads, compact_entries); the
+// refill and, in its shadow, the weights fma(sg, z, hc) are the slot-table path's,
+// with z in the entry's upper half.
+#define EP_Y_CVT_C                                                                    \
+  "v_cvt_f32_i32_sdwa %[y0], sext(%[e0]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1\n\t" \
+  "v_cvt_f32_i32_sdwa %[y1], sext(%[e1]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1\n\t" \
+  "v_fma_f32 %[y0], %[sg0], %[y0], %[hc0]\n\t"                                        \
+  "v_fma_f32 %[y1], %[sg1], %[y1], %[hc1]\n\t"
+
+#define EP_REFILL_OUTS                                                                    \
+  [x0] "+v"(x[0]), [x1] "+v"(x[1]), [SA0] "+s"(F0.OA), [D0] "+s"(F0.D), [SA1] "+s"(F1.OA), \
+      [D1] "+s"(F1.D), [t0] "=&v"(t0), [t1] "=&v"(t1), [w0] "=&v"(w0), [w1] "=&v"(w1),     \
+      [c0lo] "=&s"(c0lo), [c0hi] "=&s"(c0hi), [c1lo] "=&s"(c1lo), [c1hi] "=&s"(c1hi),     \
+      [d0] "=&s"(dd0), [d1] "=&s"(dd1), [ex] "=&s"(ex)
+
+#define EP_REFILL_INS                                                                     \
+  [vH] "v"(vH), [vrb0] "v"(vrb0), [vrb1] "v"(vrb1), [rmask] "s"(kFastRingBytes - 1),      \
+      [k15] "s"(kStateLow)
+
+#define EP_REFILL_TEMPS                                                                   \
+  uint32_t t0, t1, w0, w1, c0lo, c0hi, c1lo, c1hi, dd0, dd1;                              \
+  uint64_t ex
+
+__device__ __forceinline__ void coset_step2_c(const Hot& L, uint32_t* x, uint32_t* cb, float* hc,
+                                              const float* sg, FastChain& F0, FastChain& F1,
+                                              uint32_t vH, uint32_t vrb0, uint32_t vrb1) {
+  const uint32_t mask = (1u << L.b) - 1, bk1 = L.bk + (16u << L.ck);
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    const uint32_t u = x[j] & mask;
+    const bool c = u >= L.coset_f0;
+    x[j] = __umul24(c ? L.coset_f1 : L.coset_f0, x[j] >> L.b) + u - (c ? L.coset_f0 : 0u);
+    cb[j] = c ? bk1 : L.bk;
+    hc[j] = c ? 0.5f * sg[j] : 0.0f;
+  }
+  EP_REFILL_TEMPS;
+  asm volatile(EP_REFILL_BOTH : EP_REFILL_OUTS : EP_REFILL_INS : EP_STEP_CLOBBERS);
+}
+
+template <int KIND, int FIELD>
+__device__ __forceinline__ void field_step2_c(const Hot& L, const uint32_t* tab, uint32_t* x,
+                                              const uint32_t* cb, uint32_t* e, float* y,
+                                              const float* sg, const float* hc, const uint32_t* X,
+                                              FastChain& F0, FastChain& F1, uint32_t vH,
+                                              uint32_t vrb0, uint32_t vrb1) {
+  uint32_t en[2];
+#pragma unroll
+  for (int j = 0; j < 2; j++) compact_entries<KIND>(L, tab, FIELD, cb[j], x[j], e[j], en[j]);
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    const uint32_t F = e[j] & 0xFFFFu;
+    x[j] = __umul24((en[j] & 0xFFFFu) - F, x[j] >> L.b) + ((x[j] & ((1u << L.b) - 1)) - F);
+    if constexpr (FIELD == 8) e[j] |= X[j] & 0x10000u;   // parity: z is even for field 8
+  }
+  EP_REFILL_TEMPS;
+  asm volatile(EP_REFILL_BOTH_W(EP_Y_CVT_C)
+               : EP_REFILL_OUTS, [y0] "=&v"(y[0]), [y1] "=&v"(y[1])
+               : [e0] "v"(e[0]), [e1] "v"(e[1]), [sg0] "v"(sg[0]), [sg1] "v"(sg[1]),
+                 [hc0] "v"(hc[0]), [hc1] "v"(hc[1]), EP_REFILL_INS
+               : EP_STEP_CLOBBERS);
+}
+
 // ---- one chain per wave (small launches) ----------------------------------------
 // A launch with too few tiles to put several waves on every SIMD is bound by
 // the latency of a wave's own serial chain of symbol steps, so a wave then
@@ -1426,14 +1544,50 @@ __device__ __forceinline__ void coset_step1(uint32_t& x0, uint32_t& P, uint32_t&
       : EP_STEP1_CLOBBERS);
 }
 
+// The same steps on the compact search form (see field_step2_c).
+__device__ __forceinline__ void coset_step1_c(const Hot& L, uint32_t& x0, uint32_t& P, uint32_t& cb,
+                                              float& hc, float sg, uint32_t mlo, uint32_t vrb0) {
+  const uint32_t u = x0 & ((1u << L.b) - 1);
+  const bool c = u >= L.coset_f0;
+  x0 = __umul24(c ? L.coset_f1 : L.coset_f0, x0 >> L.b) + u - (c ? L.coset_f0 : 0u);
+  cb = c ? L.bk + (16u << L.ck) : L.bk;
+  hc = c ? 0.5f * sg : 0.0f;
+  EP_STEP1_TEMPS;
+  asm volatile(EP_REFILL_ONE_W("s_nop 0\n\t", "")
+               : EP_STEP1_OUTS
+               : [mlo] "v"(mlo), [mhi] "v"(~mlo), [vrb0] "v"(vrb0), [rmask] "s"(kOneRingBytes - 1)
+               : EP_STEP1_CLOBBERS);
+}
+
+template <int KIND, int FIELD>
+__device__ __forceinline__ void field_step1_c(const Hot& L, const uint32_t* tab, uint32_t& x0, uint32_t& P,
+                                              uint32_t cb, uint32_t& e, float& y, float sg, float hc,
+                                              uint32_t X, uint32_t mlo, uint32_t vrb0) {
+  uint32_t en;
+  compact_entries<KIND>(L, tab, FIELD, cb, x0, e, en);
+  const uint32_t F = e & 0xFFFFu;
+  x0 = __umul24((en & 0xFFFFu) - F, x0 >> L.b) + ((x0 & ((1u << L.b) - 1)) - F);
+  if constexpr (FIELD == 8) e |= X & 0x10000u;   // parity: z is even for field 8
+  EP_STEP1_TEMPS;
+  asm volatile(
+      EP_REFILL_ONE_W(
+          "v_cvt_f32_i32_sdwa %[y0], sext(%[e0]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1\n\t",
+          EP_Y_FMA1)
+      : EP_STEP1_OUTS, [y0] "=&v"(y)
+      : [e0] "v"(e), [sg0] "v"(sg), [hc0] "v"(hc), [mlo] "v"(mlo), [mhi] "v"(~mlo), [vrb0] "v"(vrb0),
+        [rmask] "s"(kOneRingBytes - 1)
+      : EP_STEP1_CLOBBERS);
+}
+
 // The payload staging of a single chain, all of it per lane (uniform over each
 // half): positions in words from the first block of the half's stream.  A half's
 // ring holds four 128-word blocks, addressed modulo its size.  A block is
 // requested into registers and committed once the ring has room for it, at the
 // start of a round and after field 4: by then it was requested at least half a
-// round earlier.  Between two such points a valid stream at b bits takes at
-// most 2 b n + 32 words in n <= 5 steps, fewer than a block, so the margin of
-// 385 words that a commit restores is never used up.
+// round earlier.  A valid stream at b bits takes at most 2 b n + 32 words in n
+// steps.  At b <= 12 that is fewer than a block in the five steps between two
+// points but for the 32, so one commit a point keeps the margin of 385 words
+// that it starts with above 192; above, each point commits until it is.
 struct OneChain {
   uint32_t P, Q;     // read position, committed end
   uint32_t C, E;     // payload word of the first block, end of the stream (from C)
@@ -1444,12 +1598,15 @@ __device__ __forceinline__ void one_fetch(OneChain& F, __amdgpu_buffer_rsrc_t rs
   F.pend = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (F.Q < F.E ? 2 * (F.C + F.Q) : kFastOob) + 8 * l, 0, 0);
 }
 
+template <bool MANY>
 __device__ __forceinline__ void one_stage(OneChain& F, uint8_t* lds, uint32_t vrb8,
                                           __amdgpu_buffer_rsrc_t rsrc, uint32_t l) {
   if (__builtin_expect(F.Q - F.P <= kOneRingWords - kFastBlockWords, 0)) {
-    *reinterpret_cast<u32x2*>(lds + vrb8 + 2 * (F.Q & (kOneRingWords - 1))) = F.pend;
-    F.Q += kFastBlockWords;
-    one_fetch(F, rsrc, l);
+    do {
+      *reinterpret_cast<u32x2*>(lds + vrb8 + 2 * (F.Q & (kOneRingWords - 1))) = F.pend;
+      F.Q += kFastBlockWords;
+      one_fetch(F, rsrc, l);
+    } while (MANY && F.Q - F.P <= kOneRingWords - 2 * kFastBlockWords);
   }
 }
 
@@ -1796,7 +1953,7 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
   if (err && status) atomicOr(status, (int32_t)err);
 }
 
-// The slot-table decode with one chain per wave: a task of two tiles, t0 in
+// The decode with one chain per wave: a task of two tiles, t0 in
 // lanes 0-31 and t0 + 1 in lanes 32-63, for launches with too few four-tile
 // tasks to fill the SIMDs, and for the fused product with more than four rows
 // of X (MT of them at most; 0 stores the weights), whose sums then fit the
@@ -1812,10 +1969,14 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
 // Otherwise the steps form the coordinates themselves and the round's scale,
 // requested at its start, multiplies them at its end: one rounding either way,
 // and no wait for memory but that one.
-template <int B, bool WIDE, int DT, bool TWO, int MT = 0>
-__device__ __forceinline__ void lut_task1(const Hot& L, uint8_t* lds, uint32_t ring_area, uint32_t t0,
+//
+// PATH: the slot-table paths at b = B, or the search path's compact form KIND.
+template <int PATH, int B, int KIND, int DT, bool TWO, int MT = 0>
+__device__ __forceinline__ void chain_task(const Hot& L, uint8_t* lds, uint32_t ring_area, uint32_t t0,
                                           int32_t* status) {
-  constexpr bool DOT = MT > 0;
+  constexpr bool DOT = MT > 0, SEARCH = PATH == kPathSearch, WIDE = PATH == kPathWide;
+  constexpr bool MANY = SEARCH && KIND == kCompactAny;   // b may be above 12
+  const uint32_t* const tab = reinterpret_cast<const uint32_t*>(lds);
   const uint32_t lane = threadIdx.x & 63, wave = wave_id();
   const uint32_t half = lane >> 5, l = lane & 31;
   const EP_GLOBAL uint32_t* states = gptr<const uint32_t>(L.blob + L.off_states);
@@ -1877,7 +2038,7 @@ __device__ __forceinline__ void lut_task1(const Hot& L, uint8_t* lds, uint32_t r
     const uint32_t i = l + 32 * k;   // this round's vector of the tile
     const bool pin = PART && i >= nv;
     const uint32_t xsave = x;
-    one_stage(F, lds, vrb08, rsrc, l);
+    one_stage<MANY>(F, lds, vrb08, rsrc, l);
     float sg = 1.0f, scale = 1.0f;
     if constexpr (TWO) sg = k < kc ? sa : sb;
     else scale = __uint_as_float(
@@ -1906,14 +2067,17 @@ __device__ __forceinline__ void lut_task1(const Hot& L, uint8_t* lds, uint32_t r
 #define EP_PIN1 \
   if constexpr (PART) x = pin ? kPinnedState : x;
     EP_PIN1
-    coset_step1<B>(x, F.P, cb, hc, sg, vf0, vf1, vcb, mlo, vrb0);
+    if constexpr (SEARCH) coset_step1_c(L, x, F.P, cb, hc, sg, mlo, vrb0);
+    else coset_step1<B>(x, F.P, cb, hc, sg, vf0, vf1, vcb, mlo, vrb0);
 #define EP_FIELD(I)                                                                     \
   EP_PIN1                                                                               \
-  field_step1<B, I, WIDE>(x, F.P, cb, e[I & 1], y[I - 1], sg, hc, X, mlo, vrb0);        \
+  if constexpr (SEARCH)                                                                 \
+    field_step1_c<KIND, I>(L, tab, x, F.P, cb, e[I & 1], y[I - 1], sg, hc, X, mlo, vrb0); \
+  else field_step1<B, I, WIDE>(x, F.P, cb, e[I & 1], y[I - 1], sg, hc, X, mlo, vrb0);   \
   if constexpr (I == 7) X ^= e[1];                                                      \
   else if constexpr (I < 7 && I % 2 == 0) X = xor3(X, e[0], e[1]);
     EP_FIELD(1) EP_FIELD(2) EP_FIELD(3) EP_FIELD(4)
-    one_stage(F, lds, vrb08, rsrc, l);
+    one_stage<MANY>(F, lds, vrb08, rsrc, l);
     if constexpr (DOT) {
       const uint32_t w = int8_quad(y[0], y[1], y[2], y[3]);
 #pragma unroll
@@ -1973,24 +2137,146 @@ __device__ __forceinline__ void lut_task1(const Hot& L, uint8_t* lds, uint32_t r
   if (err && status) atomicOr(status, (int32_t)err);
 }
 
-// Output type and row-scale variants of a two-tile slot-table task: the types
-// that small layers are decoded to have instances of their own, the rest (and
-// weights that need the explicit clamp) share one.
-template <int B, bool WIDE>
-__device__ __forceinline__ void lut_task1_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
-                                              uint32_t t0, int32_t* status) {
-  auto rows = [&](auto dt) {
-    constexpr int DT = decltype(dt)::value;
-    if (L.cvec >= 32 * ((L.V - 1) / 32)) lut_task1<B, WIDE, DT, true>(L, lds, ring_area, t0, status);
-    else lut_task1<B, WIDE, DT, false>(L, lds, ring_area, t0, status);
+// Output type and row-scale variants of a two-tile task: the types that small
+// layers are decoded to have instances of their own on the slot-table paths, the
+// rest (and weights that need the explicit clamp) share one.
+template <int PATH, int B>
+__device__ __forceinline__ void chain_task_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
+                                               uint32_t t0, int32_t* status) {
+  auto rows = [&](auto dt, auto kind) {
+    constexpr int DT = decltype(dt)::value, KIND = decltype(kind)::value;
+    if (L.cvec >= 32 * ((L.V - 1) / 32)) chain_task<PATH, B, KIND, DT, true>(L, lds, ring_area, t0, status);
+    else chain_task<PATH, B, KIND, DT, false>(L, lds, ring_area, t0, status);
   };
-  switch (L.saturate ? (uint32_t)kAnyType : L.out_dtype) {
-    case EP_BF16: rows(std::integral_constant<int, EP_BF16>{}); break;
-    case EP_FP16: rows(std::integral_constant<int, EP_FP16>{}); break;
-    case EP_FP8_E4M3: rows(std::integral_constant<int, EP_FP8_E4M3>{}); break;
-    case EP_INT8: rows(std::integral_constant<int, EP_INT8>{}); break;
-    default: rows(std::integral_constant<int, kAnyType>{}); break;
+  std::integral_constant<int, kAnyType> any;
+  if constexpr (PATH == kPathSearch) {
+    if (L.form == kCompactSlot) rows(any, std::integral_constant<int, kCompactSlot>{});
+    else if (L.form == kCompactPair) rows(any, std::integral_constant<int, kCompactPair>{});
+    else rows(any, std::integral_constant<int, kCompactAny>{});
+  } else {
+    std::integral_constant<int, 0> none;
+    switch (L.saturate ? (uint32_t)kAnyType : L.out_dtype) {
+      case EP_BF16: rows(std::integral_constant<int, EP_BF16>{}, none); break;
+      case EP_FP16: rows(std::integral_constant<int, EP_FP16>{}, none); break;
+      case EP_FP8_E4M3: rows(std::integral_constant<int, EP_FP8_E4M3>{}, none); break;
+      case EP_INT8: rows(std::integral_constant<int, EP_INT8>{}, none); break;
+      default: rows(any, none); break;
+    }
   }
+}
+
+// The steady state of the search path's compact form: four full tiles (two
+// chains), the weights stored in the layer's output type at the end of a round
+// or multiplied into X (DOT).  Row scales as in chain_task, by a uniform branch
+// (the scale loaded for a round is not used before its end).
+template <int KIND, bool DOT>
+__device__ __forceinline__ void search_task(const Hot& L, uint8_t* lds, uint32_t ring_area, uint32_t t0,
+                                            int32_t* status) {
+  const uint32_t* const tab = reinterpret_cast<const uint32_t*>(lds);
+  const uint32_t lane = threadIdx.x & 63, wave = wave_id();
+  const uint32_t half = lane >> 5, l = lane & 31;
+  const EP_GLOBAL uint32_t* states = gptr<const uint32_t>(L.blob + L.off_states);
+  const EP_GLOBAL uint32_t* offs = gptr<const uint32_t>(L.blob + L.off_offsets);
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(L.blob + L.off_payload), (short)0, (int)L.pay_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(L.blob + L.off_sigma), (short)0, (int)(4 * L.rows), 0x00020000);
+  const uint32_t vrb0 = ring_area + wave * 2 * kFastChainBytes + half * kFastRingBytes;
+  const uint32_t vrb1 = vrb0 + kFastChainBytes;
+  const uint32_t vl8 = 8 * l;
+  uint32_t o[5];
+#pragma unroll
+  for (int i = 0; i < 5; i++) o[i] = offs[t0 + i];
+  const bool coord = !DOT && L.out_dtype == EP_COORD2_I32;
+  const bool two = L.cvec >= L.V - 32;
+  uint32_t x[2], vb[2], kc[2] = {0, 0};
+  float sa[2] = {1.0f, 1.0f}, sb[2] = {1.0f, 1.0f};
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    const uint32_t tile = t0 + 2 * j + half;
+    x[j] = states[(uint64_t)tile * 32 + l];
+    vb[j] = tile * L.V + l;
+    if (two && !coord) {
+      const uint32_t r = row_of(L, vb[j]);
+      kc[j] = ((r + 1) * L.cvec - vb[j] + 31) >> 5;
+      sa[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(srsrc, 4 * r, 0, 0));
+      sb[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(srsrc, 4 * r + 4, 0, 0));
+    }
+  }
+  FastChain F0, F1;
+  u32x2 pend0, pend1, pendB0, pendB1;
+#pragma unroll
+  for (int i = 0; i < 5; i++) o[i] = uni(o[i]);
+  const u32x4 fill0 = fast_start(F0, pend0, rsrc, half, l, o[0], o[1], o[1], o[2]);
+  const u32x4 fill1 = fast_start(F1, pend1, rsrc, half, l, o[2], o[3], o[3], o[4]);
+  __builtin_amdgcn_s_waitcnt(0);   // no load in flight when the loop starts
+  *reinterpret_cast<u32x4*>(lds + vrb0 + 16 * l) = fill0;
+  *reinterpret_cast<u32x4*>(lds + vrb1 + 16 * l) = fill1;
+  pendB0 = pend0;   // pend* serve lanes 0-31, pendB* lanes 32-63
+  pendB1 = pend1;
+
+  const uint32_t vH = half, rounds = L.V / 32;
+  const uint32_t vrb08 = vrb0 + vl8, vrb18 = vrb1 + vl8;
+  for (uint32_t k = 0; k < rounds; k++) {
+    fast_stage_both(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half,
+                    kFastRingWords - kFastBlockWords + 1);
+    float sg[2], scale[2] = {1.0f, 1.0f};
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      sg[j] = k < kc[j] ? sa[j] : sb[j];
+      if (!two && !coord)
+        scale[j] = __uint_as_float(
+            __builtin_amdgcn_raw_buffer_load_b32(srsrc, 4 * row_of(L, vb[j] + 32 * k), 0, 0));
+    }
+    uint32_t cb[2], e[2], eo[2], X[2] = {0, 0};
+    float hc[2], y[8][2];
+    coset_step2_c(L, x, cb, hc, sg, F0, F1, vH, vrb0, vrb1);
+    // X: bit 16 of the xor of the entries of fields 1..7 is the parity
+#define EP_FIELD(I)                                                                            \
+  field_step2_c<KIND, I>(L, tab, x, cb, I & 1 ? eo : e, y[I - 1], sg, hc, X, F0, F1, vH, vrb0, vrb1); \
+  if constexpr (I == 7) {                                                                      \
+    X[0] ^= eo[0];                                                                             \
+    X[1] ^= eo[1];                                                                             \
+  } else if constexpr (I < 7 && I % 2 == 0) {                                                  \
+    X[0] = xor3(X[0], eo[0], e[0]);                                                            \
+    X[1] = xor3(X[1], eo[1], e[1]);                                                            \
+  }
+    EP_FIELD(1) EP_FIELD(2)
+    fast_stage_both(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
+    EP_FIELD(3) EP_FIELD(4) EP_FIELD(5)
+    fast_stage_both(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
+    EP_FIELD(6) EP_FIELD(7) EP_FIELD(8)
+#undef EP_FIELD
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const uint32_t v = vb[j] + 32 * k;
+      float w[8];
+#pragma unroll
+      for (int i = 0; i < 8; i++) w[i] = y[i][j];
+      if (!two && !coord)
+#pragma unroll
+        for (int i = 0; i < 8; i++) w[i] *= scale[j];
+      if constexpr (DOT) dot_add(L, int8_quad(w[0], w[1], w[2], w[3]), int8_quad(w[4], w[5], w[6], w[7]), v, row_of(L, v));
+      else store_weights(L, v, w);
+    }
+  }
+
+  uint32_t err = 0;
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    if (x[j] != kStateLow) err |= EP_STATUS_BAD_FINAL_STATE;
+    const FastChain& F = j ? F1 : F0;
+    const uint32_t P = half ? F.OA + F.D : F.OA, E = half ? F.EB : F.EA;
+    if (l == 0 && P != E) err |= P > E ? EP_STATUS_PAYLOAD_OVERRUN : EP_STATUS_BAD_END_OFFSET;
+    if (L.container && L.dequant) {
+      const EP_GLOBAL float* delta = gptr<const float>(L.blob + L.off_delta);
+      const uint32_t v0 = (t0 + 2 * j + half) * L.V;
+      const uint32_t r_first = (v0 + L.cvec - 1) / L.cvec;
+      const uint32_t r_last = (v0 + L.V - 1) / L.cvec;
+      for (uint32_t r = r_first + l; r <= r_last; r += 32) gptr<float>(L.dequant)[r] = delta[r];
+    }
+  }
+  if (err && status) atomicOr(status, (int32_t)err);
 }
 
 // Row-scale and sum variants of a full four-tile slot-table task.
@@ -2062,47 +2348,15 @@ __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_
   }
 }
 
-// Output-type dispatch of a full search-path task (four tiles, two chains).  Returns
-// false for the combinations the steady state does not cover (they take the generic loop).
-template <int PATH, int B, bool DOT = false>
-__device__ __forceinline__ bool decode_task_fast_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
-                                                     uint32_t task, int32_t* status) {
-  if constexpr (DOT) {
-    decode_task_fast<PATH, B, kOutDotI8, false>(L, lds, ring_area, task, status);
-    return true;
-  }
-  switch (L.out_dtype) {
-    case EP_BF16:
-      if (L.saturate) return false;
-      decode_task_fast<PATH, B, EP_BF16, false>(L, lds, ring_area, task, status);
-      return true;
-    case EP_FP16:
-      if (L.saturate) decode_task_fast<PATH, B, EP_FP16, true>(L, lds, ring_area, task, status);
-      else decode_task_fast<PATH, B, EP_FP16, false>(L, lds, ring_area, task, status);
-      return true;
-    case EP_FP8_E4M3:
-      if (L.saturate) decode_task_fast<PATH, B, EP_FP8_E4M3, true>(L, lds, ring_area, task, status);
-      else decode_task_fast<PATH, B, EP_FP8_E4M3, false>(L, lds, ring_area, task, status);
-      return true;
-    case EP_FP8_E5M2:
-      if (L.saturate) decode_task_fast<PATH, B, EP_FP8_E5M2, true>(L, lds, ring_area, task, status);
-      else decode_task_fast<PATH, B, EP_FP8_E5M2, false>(L, lds, ring_area, task, status);
-      return true;
-    case EP_INT8:
-      decode_task_fast<PATH, B, EP_INT8, false>(L, lds, ring_area, task, status);
-      return true;
-    case EP_UINT8:
-      decode_task_fast<PATH, B, EP_UINT8, false>(L, lds, ring_area, task, status);
-      return true;
-    case EP_FP32:
-      decode_task_fast<PATH, B, EP_FP32, false>(L, lds, ring_area, task, status);
-      return true;
-    case EP_COORD2_I32:
-      decode_task_fast<PATH, B, EP_COORD2_I32, false>(L, lds, ring_area, task, status);
-      return true;
-    default:
-      return false;
-  }
+// A full search-path task (four tiles, two chains), by the form of its tables.
+template <bool DOT>
+__device__ __forceinline__ void search_task_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
+                                                uint32_t task, int32_t* status) {
+  const uint32_t t0 = L.tile_begin + 4 * task;
+  if (L.form == kCompactSlot) search_task<kCompactSlot, DOT>(L, lds, ring_area, t0, status);
+  else if (L.form == kCompactPair) search_task<kCompactPair, DOT>(L, lds, ring_area, t0, status);
+  else if (L.form == kCompactAny) search_task<kCompactAny, DOT>(L, lds, ring_area, t0, status);
+  else decode_task_fast<DOT>(L, lds, ring_area, task, status);
 }
 
 // LDS byte offset of the payload rings: after the slot table (LUT path) or
@@ -2110,7 +2364,7 @@ __device__ __forceinline__ bool decode_task_fast_any(const Hot& L, uint8_t* lds,
 template <int PATH>
 __device__ __forceinline__ uint32_t ring_offset(const LayerDev& L) {
   if (PATH == kPathGlobal) return (L.g_meta + 4 * 64 + 511) & ~511u;   // GlobalLayout::total
-  return PATH != kPathSearch ? (64u << L.b) : search_layout(L.b, L.sum_A).total;
+  return PATH != kPathSearch ? (64u << L.b) : search_area(L.b, L.sum_A, L.compact != 0);
 }
 
 // Search-path tables (byte layout from search_layout): u16 cumulative values
@@ -2118,7 +2372,72 @@ __device__ __forceinline__ uint32_t ring_offset(const LayerDev& L) {
 // bucket bounds bk[t][0 .. 2^k] (bk[t][j] = the symbol whose slot range holds
 // slot j * 2^(b-k); bk[t][2^k] = A_t - 1), and u32 metadata base'[16], min[16].
 // Each symbol writes the bucket starts inside its own slot range.
+//
+// Compact form (paths.h): the waves count their tables' symbols first, so that
+// every wave knows where its entries start and whether all fit.
+__device__ __forceinline__ uint32_t build_compact(const LayerDev& L, uint32_t* lds, uint32_t area) {
+  const int lane = threadIdx.x & 63, wave = (int)wave_id();
+  uint32_t* const count = lds + area / 4;   // in the ring area
+  for (int t = wave; t < 16; t += kWavesPerGroup) {
+    const EP_GLOBAL uint16_t* f = gptr<const uint16_t>(L.blob + L.tab_off[t]);
+    const uint32_t A = L.tab_A[t];
+    uint32_t n = 0;
+    for (uint32_t s = lane; s < A; s += kWaveSize) n += f[s] != 0;
+#pragma unroll
+    for (int d = 1; d < kWaveSize; d <<= 1) n += __shfl_xor(n, d, kWaveSize);
+    if (lane == 0) count[t] = n;
+  }
+  __syncthreads();
+  uint32_t base[16], total = 0;
+#pragma unroll
+  for (int t = 0; t < 16; t++) {
+    base[t] = total;
+    total += uni(count[t]) + 1;
+  }
+  const uint32_t need = 4 * (total + 2);   // two reads past the last entry
+  const uint32_t k = need <= compact_buckets(area, kCompactBits) ? kCompactBits
+                     : need <= compact_buckets(area, kCompactBitsLow) ? kCompactBitsLow : 0u;
+  if (threadIdx.x == 0) lds[(area - kCompactTail) / 4] = k;
+  if (k == 0) return 0;
+  uint16_t* const bk = reinterpret_cast<uint16_t*>(lds) + compact_buckets(area, k) / 2;
+  const uint32_t sh = L.b > k ? L.b - k : 0, M = 1u << L.b;
+  for (int t = wave; t < 16; t += kWavesPerGroup) {
+    const EP_GLOBAL uint16_t* f = gptr<const uint16_t>(L.blob + L.tab_off[t]);
+    const uint32_t A = L.tab_A[t];
+    const int32_t mn = L.tab_min[t], zs = (t & 7) == 7 ? 1 : 0;   // field 8 stores 2m
+    uint32_t run = 0, at = base[0];
+#pragma unroll
+    for (int q = 1; q < 16; q++) at = t == q ? base[q] : at;
+    uint16_t* const row = bk + ((uint32_t)t << k);
+    for (uint32_t s0 = 0; s0 < A; s0 += kWaveSize) {
+      const uint32_t s = s0 + lane;
+      const uint32_t fs = s < A ? f[s] : 0u;
+      const uint64_t have = __ballot(fs != 0);
+      uint32_t incl = fs;
+#pragma unroll
+      for (int d = 1; d < kWaveSize; d <<= 1) {
+        const uint32_t o = __shfl_up(incl, d, kWaveSize);
+        if (lane >= d) incl += o;
+      }
+      if (fs) {
+        const uint32_t F = run + incl - fs;
+        const uint32_t i = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(have >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)have, 0u));
+        lds[i] = F | ((uint32_t)(((int32_t)s + mn) << zs) << 16);
+        for (uint32_t j = (F + (1u << sh) - 1) >> sh; j < (F + fs + (1u << sh) - 1) >> sh; j++) row[j] = (uint16_t)i;
+      }
+      run += __shfl(incl, kWaveSize - 1, kWaveSize);
+      at += (uint32_t)__builtin_popcountll(have);
+    }
+    if (lane == 0) lds[at] = M;
+    if (run == 0)   // no symbols: every bucket points at the end entry
+      for (uint32_t j = lane; j < (1u << k); j += kWaveSize) row[j] = (uint16_t)at;
+  }
+  if (threadIdx.x < 2) lds[total + threadIdx.x] = M;
+  return k;
+}
+
 __device__ __forceinline__ void build_search(const LayerDev& L, uint32_t* lds) {
+  if (L.compact && build_compact(L, lds, search_area(L.b, L.sum_A, true))) return;
   uint16_t* cum = reinterpret_cast<uint16_t*>(lds);
   const SearchLayout S = search_layout(L.b, L.sum_A);
   uint16_t* bk = cum + S.bucket / 2;
@@ -2209,19 +2528,22 @@ template <int PATH, int B, bool DOT, bool SMALL, bool STREAMS>
 __device__ __forceinline__ void task_b(const Hot& L, const uint32_t* tab, uint8_t* lb,
                                        uint32_t ring_area, uint32_t task, int32_t* status) {
   const uint32_t nvec = L.rows * L.cvec;
-  if constexpr (SMALL && (PATH == kPathLut || PATH == kPathWide) && B == 11) {
+  if constexpr (SMALL && (PATH == kPathSearch || ((PATH == kPathLut || PATH == kPathWide) && B == 11))) {
     if (L.tpt == 2) {
       // two-tile tasks, one chain per wave
       const uint32_t t0 = L.tile_begin + 2 * task;
       const bool whole = t0 + 2 <= L.tile_end && (uint64_t)(t0 + 2) * L.V <= nvec;
-      constexpr bool WIDE = PATH == kPathWide;
       if (L.pay_bytes < kFastOob) {
         if constexpr (!DOT) {
-          lut_task1_any<B, WIDE>(L, lb, ring_area, t0, status);
-          return;
-        } else if (whole && L.V % 32 == 0 && L.cvec >= L.V) {
-          lut_task1<B, WIDE, kOutDotI8, true, kDotMaxTokens>(L, lb, ring_area, t0, status);
-          return;
+          if (PATH != kPathSearch || L.form) {
+            chain_task_any<PATH, B>(L, lb, ring_area, t0, status);
+            return;
+          }
+        } else if constexpr (PATH != kPathSearch) {
+          if (whole && L.V % 32 == 0 && L.cvec >= L.V) {
+            chain_task<PATH, B, 0, kOutDotI8, true, kDotMaxTokens>(L, lb, ring_area, t0, status);
+            return;
+          }
         }
       }
       if (whole && L.V % 32 == 0) decode_task<PATH, B, 1, true, DOT>(L, tab, lb, ring_area, task, status);
@@ -2240,7 +2562,8 @@ __device__ __forceinline__ void task_b(const Hot& L, const uint32_t* tab, uint8_
     if constexpr (PATH != kPathSearch && B == 11) {
       if (lut_task_any<B, PATH == kPathWide, DOT, STREAMS>(L, lb, ring_area, t0, status)) return;
     } else if constexpr (PATH == kPathSearch) {
-      if (decode_task_fast_any<PATH, B, DOT>(L, lb, ring_area, task, status)) return;
+      search_task_any<DOT>(L, lb, ring_area, task, status);
+      return;
     }
   }
   // generic loop
@@ -2277,6 +2600,20 @@ __device__ __forceinline__ void load_tables(const LayerDev& L, uint32_t* lds) {
   __builtin_amdgcn_s_waitcnt(0);
 }
 
+// Fill in the form of a layer's search tables, once they are in LDS.
+template <int PATH>
+__device__ __forceinline__ void set_form(Hot& H, const LayerDev& L, const uint32_t* lds) {
+  if constexpr (PATH == kPathSearch) {
+    if (!uni(L.compact)) return;
+    const uint32_t area = search_area(L.b, L.sum_A, true), k = uni(lds[(area - kCompactTail) / 4]);
+    if (!k) return;
+    H.ck = k;
+    H.bk = uni(compact_buckets(area, k));
+    H.csh = H.b > k ? H.b - k : 0;
+    H.form = k == kCompactBits && H.csh <= 1 ? (H.csh ? kCompactPair : kCompactSlot) : kCompactAny;
+  }
+}
+
 // One layer segment of a workgroup: build (or copy) the layer's tables, then
 // the waves take tasks [seg, seg_end) in turn.
 template <int PATH, bool DOT, bool SMALL = false>
@@ -2287,7 +2624,8 @@ __device__ __forceinline__ void run_segment(const LayerDev& L, uint32_t* lds, ui
   __syncthreads();
   const uint32_t ring_area = uni(ring_offset<PATH>(L));
   const uint32_t first = uni(L.task_begin);
-  const Hot H = make_hot(L);
+  Hot H = make_hot(L);
+  set_form<PATH>(H, L, lds);
   uint8_t* lb = reinterpret_cast<uint8_t*>(lds);
   for (uint32_t task = seg + wave_id(); task < seg_end; task += kWavesPerGroup)
     dispatch_task<PATH, DOT, SMALL>(H, lds, lb, ring_area, task - first, status);

@@ -54,6 +54,46 @@ constexpr SearchLayout search_layout(uint32_t b, uint32_t sum_A) {
   return SearchLayout{0, 0, 0, 0};
 }
 
+// Search path, compact form.  Tables of high-rate tensors are mostly gaps: at 8
+// bits per weight a third of the symbols in a table's index range occur.  This
+// form keeps only those, one u32 each (F | z << 16, z the integer part of the
+// coordinate, 2m for field 8) and an end entry (F = 2^b) per table, and u16
+// buckets of 2^k per table that hold the index of the symbol of their first slot
+// (k = 11, or 10 when the symbols need the room).  A symbol is then one bucket
+// read, one read of consecutive entries and, for b = 12, one compare: no metadata,
+// no binary search (256 x 512 at b = 12: 82 -> 40 us, with the one-chain tasks it
+// allows; 10240 x 3840 at 8 bits per weight: 150 -> 122 us).  Whether the symbols fit is known once they are counted, in
+// the table build, which falls back to the cumulative form otherwise and says
+// which form it chose in a word at the start of the area's last 512 bytes.
+constexpr uint32_t kCompactBits = 11, kCompactBitsLow = 10;
+constexpr uint32_t kCompactTail = 512;
+constexpr int32_t kCompactValue = 65532;   // |doubled coordinate| whose z fits 16 bits
+
+constexpr uint32_t compact_buckets(uint32_t area, uint32_t k) { return area - kCompactTail - (32u << k); }
+
+// Bytes of the search path's table area; `compact`: the compact form may be tried.
+// The one-chain rings that follow need 1024-byte alignment.
+constexpr uint32_t search_area(uint32_t b, uint32_t sum_A, bool compact) {
+  const uint32_t plain = search_layout(b, sum_A).total;
+  if (!compact) return plain;
+  uint32_t want = 4 * (sum_A + 18) + (32u << kCompactBits) + kCompactTail;
+  if (sum_A > kSearchLdsBytes || want > kSearchLdsBytes) want = kSearchLdsBytes;
+  if (want < plain + kCompactTail) want = plain + kCompactTail;
+  return (want + 1023) & ~1023u;
+}
+
+// Whether the compact form may be tried: its z fit 16 bits and the cumulative
+// form, should it be needed, leaves the form word free.
+constexpr bool compact_possible(uint32_t b, uint32_t sum_A, int32_t coord2_min, int32_t coord2_max) {
+  return coord2_min >= -kCompactValue && coord2_max <= kCompactValue &&
+         ((search_layout(b, sum_A).total + kCompactTail + 1023) & ~1023u) <= kSearchLdsBytes;
+}
+
+// Whether the symbols are certain to fit (they are at most sum_A).
+constexpr bool compact_certain(uint32_t sum_A) {
+  return sum_A <= kSearchLdsBytes && 4 * (sum_A + 18) <= compact_buckets(kSearchLdsBytes, kCompactBitsLow);
+}
+
 // Global-table path (tables too large for the LDS paths; App. C.3 places the decode
 // tables in shared or packed global memory by alphabet size).  The blob's own u16
 // frequency arrays are read from global memory; LDS holds every G-th cumulative

@@ -617,3 +617,51 @@ def test_launch_larger_than_the_last_level_cache(E, oracle, name, container):
     assert all(bool((bits[i] == bits[0]).all()) for i in range(1, n))
     if container:
         assert all(np.array_equal(dq[i].cpu().numpy(), ref_dq) for i in range(n))
+
+
+def observed_symbols(blob):
+    """Symbols with a positive frequency over a blob's 16 field tables."""
+    at, n = 48 + 4, 0
+    for _ in range(16):
+        A = int(blob[at + 4:at + 8].view(np.uint32)[0])
+        n += int((blob[at + 8:at + 8 + 2 * A].view(np.uint16) > 0).sum())
+        at += 8 + (2 * A + 3) // 4 * 4
+    return n
+
+
+@pytest.mark.parametrize("tasks", TASKS)
+@pytest.mark.parametrize("case", ["slot9", "slot11", "pair", "pair_ragged", "pair_short_rows", "any13", "any15",
+                                  "one_coset", "large_k10", "too_many"])
+def test_search_tables_of_every_form(E, oracle, case, tasks):
+    """The search path on tables that take each form: one slot a bucket (b = 9 and 11), two
+    (b = 12; ragged tiles; rows shorter than a tile), more (b = 13, 15), a tensor that uses one
+    coset only, enough symbols for the coarser buckets, and more than the compact form holds."""
+    rng = np.random.default_rng(5)
+    uniform = W.f32_to_bf16_bits(rng.uniform(-1, 1, (512, 2048)).astype(np.float32))
+    ints = W.f32_to_bf16_bits(2.0 * rng.integers(-3, 4, (48, 512)).astype(np.float32))
+    gen = {
+        "slot9": lambda: oracle.encode(W.ragged_tensor(6, 64, 256), 2.0, prob_bits=9),
+        "slot11": lambda: oracle.encode(W.ragged_tensor(7, 96, 1024), 4.0, tile_vectors=64),
+        "pair": lambda: oracle.encode(W.ragged_tensor(8, 96, 2048), 8.0, prob_bits=12, tile_vectors=96),
+        "pair_ragged": lambda: oracle.encode(W.ragged_tensor(9, 61, 1000), 6.0, prob_bits=12, tile_vectors=45),
+        "pair_short_rows": lambda: oracle.encode(W.ragged_tensor(10, 500, 72), 5.0, prob_bits=12, tile_vectors=128),
+        "any13": lambda: oracle.encode(W.ragged_tensor(11, 96, 1024), 5.0, prob_bits=13, tile_vectors=160),
+        "any15": lambda: oracle.encode(W.ragged_tensor(12, 96, 1024), 9.0, prob_bits=15, tile_vectors=64),
+        "one_coset": lambda: oracle.encode(ints, 2.0, prob_bits=12, scale_lo=0.5, scale_hi=0.5),
+        "large_k10": lambda: oracle.encode(uniform, 11.0, prob_bits=15),
+        "too_many": lambda: oracle.encode(uniform, 12.4, prob_bits=15),
+    }[case]
+    blob, _ = gen()
+    info = E.blob_info(blob)
+    n = observed_symbols(blob)
+    say(f"    {case}: b={info.prob_bits} symbols={n} sum_A={info.sum_alphabet}")
+    # entries of the compact form: with buckets of 11 bits, of 10 bits
+    if case == "large_k10":
+        assert 16 * 1024 <= n <= 24400
+    elif case == "too_many":
+        assert n > 24500 and search_fits(info.prob_bits, info.sum_alphabet)
+    else:
+        assert n < 16000
+    with task_mode(tasks):
+        check_blob(E, oracle, blob, dtypes=["COORD2", "BF16", "FP16", "FP32", "FP8", "INT8"],
+                   tag=f"{case} {tasks}", path=2)
