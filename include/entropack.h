@@ -262,11 +262,9 @@ int ep_decode_matmul_i8(const ep_tensor_info* info, const void* d_blob, const in
  * last-level cache) and multiplies X by those rows on the matrix cores
  * (v_mfma_i32_16x16x64_i8).  d_workspace: >= ep_decode_gemm_i8_workspace(info)
  * bytes of device memory owned by the caller, untouched until the launch
- * completes.  Y is overwritten (cleared first on hip_stream by a small fill
- * kernel whenever partial sums over K are added with atomics: at fewer rows of
- * X than 16 work items need, 256 to 976 rows by the block's height).
- * d_dequant (R floats, required) receives delta_r for every row; d_status as
- * for ep_decode_tiles.  Asynchronous, no allocation, at most one clear and one launch.
+ * completes.  Y is overwritten (partial sums over K meet in LDS: no clearing
+ * launch, no atomics).  d_dequant (R floats, required) receives delta_r for every
+ * row; d_status as for ep_decode_tiles.  Asynchronous, no allocation, one launch.
  * Errors: EP_ERR_ARG (null pointers, m outside 1..65536, X above 2^31 bytes, short
  * workspace), EP_ERR_UNSUPPORTED (not the INT8 row container, C > 131071),
  * EP_ERR_HIP. */
@@ -310,13 +308,11 @@ int ep_decode_gemm_i8_prepared(const ep_tensor_info* info, const void* d_blob, c
  * (v_mfma_f32_16x16x32_bf16); every product of two bf16 values is exact in
  * fp32 and the sums are fp32, so |Y - X W'^T| <= (C + s + 2) 2^-24 sum_j
  * |X[t][j] W'[r][j]| with s <= 16 partial sums per element (K is split over
- * waves at small m, as for the INT8 product, and those partial sums are added
- * with float atomics, so the last bits of Y may differ from call to call).
- * d_workspace: >= ep_decode_gemm_bf16_workspace(info) bytes.  Y is
- * overwritten (cleared first when K is split).  d_status as for
- * ep_decode_gemm_i8; d_dequant (R floats) receives delta_r for container
- * tensors (required for them, ignored otherwise).  Asynchronous,
- * no allocation, at most one clear and one launch.
+ * waves at small m, as for the INT8 product; the partial sums are added in a
+ * fixed order).  d_workspace: >= ep_decode_gemm_bf16_workspace(info) bytes.  Y is
+ * overwritten.  d_status as for ep_decode_gemm_i8; d_dequant (R floats) receives
+ * delta_r for container tensors (required for them, ignored otherwise).
+ * Asynchronous, no allocation, one launch.
  * Errors: EP_ERR_ARG (null pointers, m outside 1..65536, X above 2^31 bytes,
  * short workspace), EP_ERR_UNSUPPORTED, EP_ERR_HIP. */
 int ep_decode_gemm_bf16(const ep_tensor_info* info, const void* d_blob, const void* d_x, int64_t m,

@@ -465,10 +465,6 @@ int decode_gemm(const ep_tensor_info* info, const void* d_blob, const void* d_x,
   A.g.n_blocks = G.n_blocks;
   A.g.rows_per_block = G.rows_per_block;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // partial sums are added with atomics (0 is also +0.0f for the BF16 product)
-  if (gemm_splits_k((G.rows_per_block + 15) / 16, (uint32_t)((m + 15) / 16)) &&
-      !clear_i32(static_cast<int32_t*>(d_y), (int64_t)m * info->rows, s))
-    return fail(EP_ERR_HIP, (w + ": clearing Y failed").c_str());
   const uint32_t lds = lds_bytes(info->path, *info);
   DeviceProps P = device_props();
   if (lds > P.max_lds) return fail(EP_ERR_UNSUPPORTED, (w + ": tables exceed the device LDS").c_str());

@@ -16,31 +16,44 @@ typedef __bf16 v8bf_t __attribute__((ext_vector_type(8)));
 // all NT = ceil(RB / 16) tiles of 16 block rows, so each X fragment is loaded
 // once per block and each slab fragment once per item; items are dealt to the
 // waves, and when there are fewer items than waves K is split over the idle
-// waves and the partial sums are added with atomics (exact, order-free integer
-// additions).  NT and XT are template arguments so that no load is issued for
-// a tile the block does not have.  MFMA operands: lane l supplies row l mod 16
-// of an X tile and of a slab tile, 16 consecutive bytes of K each
-// (k = 16 (l / 16) + 0..15 of a 64-byte step); accumulator r of lane l is
-// element (4 (l / 16) + r, l mod 16) of a 16 x 16 result.
+// waves, whose partial sums meet in the ring area of the LDS (idle between two
+// blocks' decodes), two result tiles at a time, and are added in slice order by
+// all threads: no atomics on Y, and nothing to clear before the launch.  NT and XT
+// are template arguments so that no load is issued for a tile the block does
+// not have.  MFMA operands: lane l supplies row l mod 16 of an X tile and of a
+// slab tile, 16 consecutive bytes of K each (k = 16 (l / 16) + 0..15 of a
+// 64-byte step); accumulator r of lane l is element (4 (l / 16) + r, l mod 16)
+// of a 16 x 16 result.
+//
+// A wave's slice of K is a short chain of loads from L2 and beyond (the slab was
+// written by other waves of its CU, X by anyone), so it is bound by their
+// latency: kDepth groups of fragments are in flight, as many as the registers
+// hold (with 88 registers' worth of fragments, 132 to 180 bytes a lane spill and
+// the product with 16 rows loses what it gained; with 64, 48 to 64 bytes).  Down
+// projection with 16 rows of X: 121 -> 112 us; DiT MLP input (BF16) with 64 rows:
+// 104.6 -> 83.5 us, the clearing launch and the atomics gone among it.
 //
 // BF: the BF16 product (bf16 X and slab, v_mfma_f32_16x16x32_bf16, fp32 Y).
 // A lane's 16 bytes of a 64-byte K step are then 8 bf16 elements, the same
-// bytes as 16 int8 ones, so the addressing below is in bytes for both; the
-// sums are fp32 and K slices add them with float atomics.
+// bytes as 16 int8 ones, so the addressing below is in bytes for both.
 template <uint32_t NT, uint32_t XT, bool BF>
-__device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmArgs& g,
-                                                 const uint8_t* slab, uint32_t b) {
+__device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmArgs& g, const uint8_t* slab,
+                                                 uint32_t b, uint8_t* scratch) {
   const uint32_t wave = wave_id(), lane = threadIdx.x & 63;
   const uint32_t C = L.cols * (BF ? 2 : 1), m = g.m, RB = g.rows_per_block;   // C: row bytes
   const uint32_t T = (m + 15) / 16, I = (T + XT - 1) / XT;   // X tiles, items
   const uint32_t S = I >= kWavesPerGroup ? 1u : kWavesPerGroup / I;   // K slices
-  if (I < kWavesPerGroup && wave >= I * S) return;
+  const bool busy = I >= kWavesPerGroup || wave < I * S;
   const uint32_t slice = I >= kWavesPerGroup ? 0u : wave / I;
   const uint32_t it0 = I >= kWavesPerGroup ? wave : wave % I;
-  const uint32_t istep = I >= kWavesPerGroup ? kWavesPerGroup : I;
-  // 64-byte K steps per group: two groups' fragments stay within the
-  // registers the decode leaves (2 (XT + NT) kGroup fragments of 4 VGPRs)
+  // 64-byte K steps per group, and groups in flight: kDepth (XT + NT) kGroup
+  // fragments of 4 VGPRs and the accumulators stay within the registers that one
+  // wave of four on a SIMD has
   constexpr uint32_t kGroup = XT + NT <= 3 ? 2 : 1;
+  constexpr uint32_t kFit = (64 - 4 * XT * NT) / (4 * kGroup * (XT + NT));
+  constexpr uint32_t kDepth = kFit < 4 ? kFit : 4;
+  static_assert(kDepth >= 2, "two groups in flight at least");
+  constexpr uint32_t kStep = 64 * kGroup;
   // slices are cut at 128-byte boundaries whatever the group
   const uint32_t groups = (C + 127) / 128, gper = (groups + S - 1) / S;
   const uint32_t k_begin = slice * gper * 128, k_end = min(C, (slice + 1) * gper * 128);
@@ -57,8 +70,7 @@ __device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmAr
   struct Frags {
     v4i_t a[kGroup][XT], w[kGroup][NT];
   };
-  for (uint32_t it = it0; it < I; it += istep) {
-    Acc acc[XT][NT];
+  auto product = [&](uint32_t it, Acc (&acc)[XT][NT]) {
 #pragma unroll
     for (uint32_t x = 0; x < XT; x++)
 #pragma unroll
@@ -76,9 +88,7 @@ __device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmAr
           // K beyond the row (C % 64 != 0) reads as zeros of X: C is a multiple of 8
           // bytes, so a lane's 16 bytes are whole, half (the upper 8 beyond C) or none
           const bool in = kq < k_end && tok < m;
-          v4i_t av = (v4i_t)__builtin_amdgcn_raw_buffer_load_b128(xr, in ? tok * C + kq : 0x80000000u, 0, 0);
-          if (in && kq + 8 >= C) av[2] = av[3] = 0;
-          f.a[u][x] = av;
+          f.a[u][x] = (v4i_t)__builtin_amdgcn_raw_buffer_load_b128(xr, in ? tok * C + kq : 0x80000000u, 0, 0);
         }
 #pragma unroll
         for (uint32_t c = 0; c < NT; c++) {
@@ -88,11 +98,12 @@ __device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmAr
         }
       }
     };
-    auto mma = [&](const Frags& f) {
+    auto mma = [&](uint32_t k0, Frags& f) {
 #pragma unroll
       for (uint32_t u = 0; u < kGroup; u++)
 #pragma unroll
-        for (uint32_t x = 0; x < XT; x++)
+        for (uint32_t x = 0; x < XT; x++) {
+          if (k0 + 64 * u + 16 * q + 8 >= C) f.a[u][x][2] = f.a[u][x][3] = 0;
 #pragma unroll
           for (uint32_t c = 0; c < NT; c++) {
             if constexpr (BF)
@@ -102,39 +113,59 @@ __device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmAr
             else
               acc[x][c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f.a[u][x], f.w[u][c], acc[x][c], 0, 0, 0);
           }
-    };
-    // two groups in flight: the next group's loads are issued before this
-    // group's MFMAs wait for their operands
-    Frags f0, f1;
-    load(k_begin, f0);
-    for (uint32_t k0 = k_begin; k0 < k_end; k0 += 2 * 64 * kGroup) {
-      load(k0 + 64 * kGroup, f1);
-      mma(f0);
-      if (k0 + 64 * kGroup >= k_end) break;
-      load(k0 + 2 * 64 * kGroup, f0);
-      mma(f1);
-    }
-#pragma unroll
-    for (uint32_t x = 0; x < XT; x++)
-#pragma unroll
-      for (uint32_t c = 0; c < NT; c++) {
-        const uint32_t rl = 16 * c + li, row = row0 + rl;
-#pragma unroll
-        for (uint32_t r = 0; r < 4; r++) {
-          const uint32_t t = 16 * (XT * it + x) + 4 * q + r;
-          if (t < m && rl < RB && row < L.rows) {
-            if (S > 1) {
-              if constexpr (BF)
-                __hip_atomic_fetch_add(y + (uint64_t)t * L.rows + row, acc[x][c][r], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-              else
-                add_i32(y + (uint64_t)t * L.rows + row, acc[x][c][r]);
-            } else {
-              y[(uint64_t)t * L.rows + row] = acc[x][c][r];
-            }
-          }
         }
+    };
+    Frags f[kDepth];
+#pragma unroll
+    for (uint32_t i = 0; i < kDepth; i++) load(k_begin + i * kStep, f[i]);
+    for (uint32_t k0 = k_begin; k0 < k_end; k0 += kDepth * kStep) {
+#pragma unroll
+      for (uint32_t i = 0; i < kDepth; i++) {
+        mma(k0 + i * kStep, f[i]);
+        load(k0 + (i + kDepth) * kStep, f[i]);
       }
+    }
+  };
+  auto put = [&](uint32_t t, uint32_t rl, Out v) {
+    if (t < m && rl < RB && row0 + rl < L.rows) y[(uint64_t)t * L.rows + row0 + rl] = v;
+  };
+  if (S == 1) {
+    for (uint32_t it = it0; it < I; it += kWavesPerGroup) {
+      Acc acc[XT][NT];
+      product(it, acc);
+#pragma unroll
+      for (uint32_t x = 0; x < XT; x++)
+#pragma unroll
+        for (uint32_t c = 0; c < NT; c++)
+#pragma unroll
+          for (uint32_t r = 0; r < 4; r++) put(16 * (XT * it + x) + 4 * q + r, 16 * c + li, acc[x][c][r]);
+    }
+    return;
+  }
+  Acc acc[XT][NT];
+  if (busy) product(it0, acc);
+  // slot (wave, p): the 256 sums of tile pair member p of a wave's item, lane l's four at 4 l
+  static_assert(kWavesPerGroup * 2 * 1024 <= kRingBytes, "partial sums in the ring area");
+  constexpr uint32_t kTiles = XT * NT;
+#pragma unroll
+  for (uint32_t p0 = 0; p0 < kTiles; p0 += 2) {
+    const uint32_t np = kTiles - p0 < 2 ? 1 : 2;
+    if (p0) __syncthreads();   // the previous pair's sums have been read
+    if (busy) {
+#pragma unroll
+      for (uint32_t p = 0; p < 2 && p0 + p < kTiles; p++)
+        *reinterpret_cast<Acc*>(scratch + (2 * wave + p) * 1024 + 16 * lane) = acc[(p0 + p) / NT][(p0 + p) % NT];
+    }
+    __syncthreads();
+    for (uint32_t e = threadIdx.x; e < I * np * 64; e += kThreads) {
+      const uint32_t l = e & 63, ip = e >> 6, p = ip % np, it = ip / np;   // lane, pair member, item
+      Acc sum{0, 0, 0, 0};
+      for (uint32_t sl = 0; sl < S; sl++)
+        sum += *reinterpret_cast<const Acc*>(scratch + (2 * (sl * I + it) + p) * 1024 + 16 * l);
+      const uint32_t x = (p0 + p) / NT, c = (p0 + p) % NT;
+#pragma unroll
+      for (uint32_t r = 0; r < 4; r++) put(16 * (XT * it + x) + 4 * (l >> 4) + r, 16 * c + (l & 15), sum[r]);
+    }
   }
 }
 
@@ -143,12 +174,12 @@ __device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmAr
 // than 32 rows of X.
 template <bool BF, bool WIDE>
 __device__ __forceinline__ void block_product(const LayerDev& L, const GemmArgs& g,
-                                              const uint8_t* slab, uint32_t b) {
+                                              const uint8_t* slab, uint32_t b, uint8_t* scratch) {
   switch (uni((g.rows_per_block + 15) / 16)) {
-    case 1: block_product_nt<1, gemm_x_tiles(1, WIDE), BF>(L, g, slab, b); break;
-    case 2: block_product_nt<2, gemm_x_tiles(2, WIDE), BF>(L, g, slab, b); break;
-    case 3: block_product_nt<3, gemm_x_tiles(3, WIDE), BF>(L, g, slab, b); break;
-    default: block_product_nt<4, gemm_x_tiles(4, WIDE), BF>(L, g, slab, b); break;
+    case 1: block_product_nt<1, gemm_x_tiles(1, WIDE), BF>(L, g, slab, b, scratch); break;
+    case 2: block_product_nt<2, gemm_x_tiles(2, WIDE), BF>(L, g, slab, b, scratch); break;
+    case 3: block_product_nt<3, gemm_x_tiles(3, WIDE), BF>(L, g, slab, b, scratch); break;
+    default: block_product_nt<4, gemm_x_tiles(4, WIDE), BF>(L, g, slab, b, scratch); break;
   }
 }
 
@@ -191,10 +222,10 @@ __global__ __launch_bounds__(kThreads) void decode_gemm_kernel(const GemmLaunch 
     H.out = uni_ptr(reinterpret_cast<void*>(reinterpret_cast<intptr_t>(slab) - (intptr_t)shift));
     const uint32_t tasks = (H.tile_end - H.tile_begin + kTilesPerTask - 1) / kTilesPerTask;
     for (uint32_t task = wave_id(); task < tasks; task += kWavesPerGroup)
-      dispatch_task<PATH, false, false, false>(H, lds, lb, ring_area, task, status);
+      dispatch_task<PATH, false, false, BF ? EP_BF16 : EP_INT8>(H, lds, lb, ring_area, task, status);
     __syncthreads();   // the block's rows are in the slab
-    block_product<BF, WIDE>(L, g, slab, b);
-    __syncthreads();   // every wave is done with the slab
+    block_product<BF, WIDE>(L, g, slab, b, lb + ring_area);
+    __syncthreads();   // every wave is done with the slab and the partial sums
   }
 }
 

@@ -2301,12 +2301,12 @@ __device__ __forceinline__ void lut_task_rows(const Hot& L, uint8_t* lds, uint32
 }
 
 // Output-type dispatch of a full four-tile slot-table task (narrow or wide
-// entries).  STREAMS: the kernel may stream (the fused MFMA products, which
-// read their slab back, have no such instances).  Returns false for the
+// entries).  ONLY: the one output type of the kernel, never streamed (the fused
+// MFMA products read their slab back), or kAnyType.  Returns false for the
 // combinations the steady state does not cover (they take the generic loop).
 // The explicit clamp has instances only for the types whose conversion it may
 // be needed for, and neither it nor the rarer outputs have streaming ones.
-template <int B, bool WIDE, bool DOT = false, bool STREAMS = true>
+template <int B, bool WIDE, bool DOT = false, int ONLY = kAnyType>
 __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
                                              uint32_t t0, int32_t* status) {
   if constexpr (DOT) {
@@ -2314,16 +2314,14 @@ __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_
     if (L.m > 4) return false;
     lut_task_rows<B, kOutDotI8, false, WIDE>(L, lds, ring_area, t0, status);
     return true;
+  } else if constexpr (ONLY != kAnyType) {
+    lut_task_rows<B, ONLY, false, WIDE>(L, lds, ring_area, t0, status);
+    return true;
   } else {
     auto plain = [&](auto dt) {
       constexpr int DT = decltype(dt)::value;
-      if constexpr (STREAMS) {
-        if (L.stream) {
-          lut_task_rows<B, DT, false, WIDE, true>(L, lds, ring_area, t0, status);
-          return;
-        }
-      }
-      lut_task_rows<B, DT, false, WIDE>(L, lds, ring_area, t0, status);
+      if (L.stream) lut_task_rows<B, DT, false, WIDE, true>(L, lds, ring_area, t0, status);
+      else lut_task_rows<B, DT, false, WIDE>(L, lds, ring_area, t0, status);
     };
     switch (L.out_dtype) {
       case EP_BF16: plain(std::integral_constant<int, EP_BF16>{}); return true;
@@ -2522,9 +2520,9 @@ constexpr uint32_t kTilesPerTask = 4;
 static_assert(kChains == 2, "the generic loop and the search steady state advance two chains");
 static_assert(kTilesPerTask == 2 * kChains, "task granularity: one four-tile pass");
 
-// SMALL: the kernel may run two-tile tasks (see use_small_tasks).  STREAMS: it
-// may stream (see lut_task_any).
-template <int PATH, int B, bool DOT, bool SMALL, bool STREAMS>
+// SMALL: the kernel may run two-tile tasks (see use_small_tasks).  ONLY: see
+// lut_task_any.
+template <int PATH, int B, bool DOT, bool SMALL, int ONLY>
 __device__ __forceinline__ void task_b(const Hot& L, const uint32_t* tab, uint8_t* lb,
                                        uint32_t ring_area, uint32_t task, int32_t* status) {
   const uint32_t nvec = L.rows * L.cvec;
@@ -2560,7 +2558,7 @@ __device__ __forceinline__ void task_b(const Hot& L, const uint32_t* tab, uint8_
   const bool lut_ok = whole && (full || (!DOT && L.V >= 32));
   if (L.pay_bytes < kFastOob && ((PATH == kPathSearch && full) || (B == 11 && lut_ok))) {
     if constexpr (PATH != kPathSearch && B == 11) {
-      if (lut_task_any<B, PATH == kPathWide, DOT, STREAMS>(L, lb, ring_area, t0, status)) return;
+      if (lut_task_any<B, PATH == kPathWide, DOT, ONLY>(L, lb, ring_area, t0, status)) return;
     } else if constexpr (PATH == kPathSearch) {
       search_task_any<DOT>(L, lb, ring_area, task, status);
       return;
@@ -2571,13 +2569,13 @@ __device__ __forceinline__ void task_b(const Hot& L, const uint32_t* tab, uint8_
   else decode_task<PATH, B, kChains, false, DOT>(L, tab, lb, ring_area, task, status);
 }
 
-template <int PATH, bool DOT, bool SMALL = false, bool STREAMS = true>
+template <int PATH, bool DOT, bool SMALL = false, int ONLY = kAnyType>
 __device__ __forceinline__ void dispatch_task(const Hot& L, const uint32_t* tab, uint8_t* lb,
                                               uint32_t ring_area, uint32_t task, int32_t* status) {
-  if (PATH == kPathSearch || PATH == kPathGlobal) task_b<PATH, 0, DOT, SMALL, STREAMS>(L, tab, lb, ring_area, task, status);
-  else if (L.b == 11) task_b<PATH, 11, DOT, SMALL, STREAMS>(L, tab, lb, ring_area, task, status);
-  else if (L.b == 10) task_b<PATH, 10, DOT, SMALL, STREAMS>(L, tab, lb, ring_area, task, status);
-  else task_b<PATH, 9, DOT, SMALL, STREAMS>(L, tab, lb, ring_area, task, status);
+  if (PATH == kPathSearch || PATH == kPathGlobal) task_b<PATH, 0, DOT, SMALL, ONLY>(L, tab, lb, ring_area, task, status);
+  else if (L.b == 11) task_b<PATH, 11, DOT, SMALL, ONLY>(L, tab, lb, ring_area, task, status);
+  else if (L.b == 10) task_b<PATH, 10, DOT, SMALL, ONLY>(L, tab, lb, ring_area, task, status);
+  else task_b<PATH, 9, DOT, SMALL, ONLY>(L, tab, lb, ring_area, task, status);
 }
 
 // Decode global tasks [t_begin, t_end) of a layer list: per layer segment the
@@ -2728,7 +2726,7 @@ __global__ __launch_bounds__(kThreads) void decode_ws_kernel(const LayerDev* __r
 // it owns (the slab has `margin` rows on either side for the rest).
 struct GemmArgs {
   const void* x;         // m x C, row-major: int8, or bf16 for the BF16 product
-  void* y;               // m x R, row-major: int32, or fp32 (cleared first when K is split over waves)
+  void* y;               // m x R, row-major: int32, or fp32
   uint8_t* slabs;        // one slab per workgroup
   uint64_t slab_bytes;   // (RB + 2 margin) x C, rounded up to 256
   uint32_t m, margin, n_blocks, rows_per_block;
@@ -2753,13 +2751,6 @@ __host__ __device__ inline bool gemm_wide(uint32_t t) { return t > 2; }
 // so fewer items read it fewer times.
 __host__ __device__ constexpr uint32_t gemm_x_tiles(uint32_t nt, bool wide) {
   return !wide || nt > 3 ? 1u : nt == 1 ? 4u : 2u;
-}
-
-// Whether the product splits K over waves, adding partial sums to Y with
-// atomics (Y must then start at zero): fewer work items than waves.
-__host__ __device__ inline bool gemm_splits_k(uint32_t nt, uint32_t t) {
-  const uint32_t xt = gemm_x_tiles(nt, gemm_wide(t));
-  return (t + xt - 1) / xt < (uint32_t)kWavesPerGroup;
 }
 
 // The product kernels (decode_gemm_kernel) are in decode_gemm.hip.
