@@ -86,6 +86,7 @@ struct LayerDev {
   uint32_t rows, cols, cvec, b, V, n_tiles, container;
   uint32_t tile_begin, tile_end;  // tiles decoded
   uint32_t task_begin, n_tasks;   // this layer's slice of the global task list
+  uint32_t wg_begin, wg_tasks;    // workgroups of one layer each: its first, and tasks of each
   uint32_t out_dtype, saturate;
   uint32_t coset_f0, coset_f1;
   uint32_t sum_A;
@@ -422,61 +423,91 @@ __device__ __forceinline__ void store_weights(const Hot& L, uint32_t v, float* y
 }
 
 // ---- table construction in LDS ------------------------------------------------
-// Prefix sums of the 16 field tables' frequencies: put(t, s, F_s, f_s) for every
-// symbol s of table t, and end(t, M) once per table with the total (= 2^b).
-// Wave w scans table w (and w + kWavesPerGroup ... when fewer waves exist).
-// The frequencies of up to kScanAhead chunks of 64 symbols are requested
-// together before any of them is scanned, so a table of a few hundred symbols
-// waits for memory once rather than once per chunk (every workgroup builds its
-// tables at the same moment, when loads are slowest).  Lanes past the end read
-// the table's last entry (in bounds) and use 0.
-constexpr int kScanAhead = 4;
-template <class Put, class End>
-__device__ __forceinline__ void scan_tables(const LayerDev& L, Put put, End end) {
-  const int lane = threadIdx.x & 63, wave = (int)wave_id();
-  for (int t = wave; t < 16; t += kWavesPerGroup) {
-    const EP_GLOBAL uint16_t* f = gptr<const uint16_t>(L.blob + L.tab_off[t]);
-    const uint32_t A = L.tab_A[t];
-    uint32_t running = 0;
-    for (uint32_t g0 = 0; g0 < A; g0 += kScanAhead * kWaveSize) {
-      uint32_t fa[kScanAhead];
-#pragma unroll
-      for (int k = 0; k < kScanAhead; k++) {
-        const uint32_t s = g0 + k * kWaveSize + lane;
-        const uint32_t v = f[s < A ? s : A - 1];
-        fa[k] = s < A ? v : 0u;
-      }
-#pragma unroll
-      for (int k = 0; k < kScanAhead; k++) {
-        const uint32_t s0 = g0 + k * kWaveSize;
-        if (s0 >= A) break;
-        const uint32_t s = s0 + lane, fs = fa[k];
-        uint32_t incl = fs;
-#pragma unroll
-        for (int d = 1; d < kWaveSize; d <<= 1) {
-          uint32_t o = __shfl_up(incl, d, kWaveSize);
-          if (lane >= d) incl += o;
-        }
-        if (s < A) put(t, s, running + incl - fs, fs);
-        running += __shfl(incl, kWaveSize - 1, kWaveSize);
-      }
-    }
-    if (lane == 0) end(t, running);
-  }
+// Wave w builds table w: field (w mod 8) + 1 under coset w / 8.
+static_assert(kWavesPerGroup == 16, "one wave per field table");
+
+// Inclusive sum over the wave's lanes (DPP moves: no LDS round trips).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);   // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);   // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);   // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31
+  return v;
 }
 
-// Cumulative entries F_s | f_s << 16 at cum[base_t + s] (slot-table build).
-__device__ __forceinline__ void build_cumulative(const LayerDev& L, uint32_t* cum) {
-  scan_tables(L, [&](int t, uint32_t s, uint32_t F, uint32_t f) { cum[L.tab_base[t] + s] = F | (f << 16); },
-              [](int, uint32_t) {});
+// Prefix sums of the wave's table's frequencies: put(s, F_s, f_s, i) for every
+// symbol s of its index range, where i counts the symbols of positive frequency
+// before s.  Returns their number; `total` gets the sum of the frequencies (2^b,
+// or 0 for an empty table).  The frequencies of kScanAhead chunks of 64
+// symbols are requested together and the next batch before this one is scanned:
+// every workgroup builds its tables at the same moment, when loads are slowest.
+// (Batches of 8 cost the kernels registers and the fused product 3 us.)
+// Lanes past the end read the table's last entry (in bounds) and use 0.
+constexpr int kScanAhead = 4;
+template <class Put>
+__device__ __forceinline__ uint32_t scan_table(const LayerDev& L, Put put, uint32_t& total) {
+  const uint32_t lane = threadIdx.x & 63, t = wave_id();
+  const EP_GLOBAL uint16_t* f = gptr<const uint16_t>(L.blob + L.tab_off[t]);
+  const uint32_t A = uni(L.tab_A[t]);
+  uint32_t run = 0, n = 0, fa[kScanAhead], fb[kScanAhead];
+  auto fetch = [&](uint32_t g0, uint32_t* v) {
+#pragma unroll
+    for (int k = 0; k < kScanAhead; k++) {
+      const uint32_t s = g0 + k * kWaveSize + lane;
+      v[k] = f[s < A ? s : A - 1];
+    }
+  };
+  if (A) fetch(0, fa);
+  for (uint32_t g0 = 0; g0 < A; g0 += kScanAhead * kWaveSize) {
+    if (g0 + kScanAhead * kWaveSize < A) fetch(g0 + kScanAhead * kWaveSize, fb);
+#pragma unroll
+    for (int k = 0; k < kScanAhead; k++) {
+      const uint32_t s0 = g0 + k * kWaveSize;
+      if (s0 >= A) break;
+      const uint32_t s = s0 + lane, fs = s < A ? fa[k] : 0u;
+      const uint32_t incl = wave_scan(fs);
+      const uint64_t have = __ballot(fs != 0);
+      if (s < A)
+        put(s, run + incl - fs, fs,
+            n + __builtin_amdgcn_mbcnt_hi((uint32_t)(have >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)have, 0u)));
+      run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+      n += (uint32_t)__builtin_popcountll(have);
+    }
+#pragma unroll
+    for (int k = 0; k < kScanAhead; k++) fa[k] = fb[k];
+  }
+  total = run;
+  return n;
+}
+
+// Symbols of positive frequency in the wave's table.
+__device__ __forceinline__ uint32_t count_table(const LayerDev& L) {
+  const uint32_t lane = threadIdx.x & 63, t = wave_id();
+  const EP_GLOBAL uint16_t* f = gptr<const uint16_t>(L.blob + L.tab_off[t]);
+  const uint32_t A = uni(L.tab_A[t]);
+  uint32_t n = 0;
+  for (uint32_t g0 = 0; g0 < A; g0 += kScanAhead * kWaveSize) {
+    uint32_t v[kScanAhead];
+#pragma unroll
+    for (int k = 0; k < kScanAhead; k++) {
+      const uint32_t s = g0 + k * kWaveSize + lane;
+      v[k] = f[s < A ? s : A - 1];
+    }
+#pragma unroll
+    for (int k = 0; k < kScanAhead; k++)
+      n += (uint32_t)__builtin_popcountll(__ballot(v[k] != 0 && g0 + k * kWaveSize + lane < A));
+  }
+  return n;
 }
 
 __device__ __forceinline__ int32_t doubled_value(int32_t z, int field, uint32_t c) {
   return field < 8 ? 2 * z + (int32_t)c : 4 * z + (int32_t)c;
 }
 
-// Packed slot table: lut[t * M + u] for the 16 field tables (b <= 11).  Wave
-// w fills tables w, w + kWavesPerGroup, ...; each lane a run of M/64 slots.
+// Packed slot table: lut[t * M + u] for the 16 field tables (b <= 11), each lane
+// filling a run of M/64 slots of its wave's table.
 // The byte z of an entry is the field value for fields 1-7 and twice the
 // value m for field 8, so that every coordinate is 2z + c before field 8's
 // parity bit (2 pi) is added; the host admits a tensor to this path only when
@@ -484,12 +515,20 @@ __device__ __forceinline__ int32_t doubled_value(int32_t z, int field, uint32_t 
 // Wide entries (WIDE) hold f - 1 in 11 bits (f = 2^b only for a one-symbol
 // table), u - F in 11 bits and z in a signed 10-bit field: doubled coordinates
 // in [-1024, 1023].
+//
+// sym: the table's symbols of positive frequency in LDS (n of them), packed as
+// F | (f - 1) << 11 | s << 22.  Most of a table's index range may be symbols that
+// never occur: walking over those was most of the build, and with them gone a
+// step from slot to slot advances by one symbol at most, read one step ahead.
+// What a build adds to a launch, against tables prepared before: index ranges of
+// 800 in all 10 -> 7 us, of 3,000 (wide) 20 -> 7 us; the compact search form's
+// of 34,000 33 -> 15 us.
 template <bool WIDE>
-__device__ __forceinline__ void build_lut_table(const LayerDev& L, uint32_t* lut,
-                                                const uint32_t* cum, int t, int j) {
+__device__ __forceinline__ void fill_lut_table(const LayerDev& L, uint32_t* lut, const uint32_t* sym,
+                                               uint32_t n) {
+  const uint32_t t = wave_id(), j = threadIdx.x & 63;
   const uint32_t M = 1u << L.b;
   const uint32_t per = M / 64;
-  const uint32_t A = L.tab_A[t], base = L.tab_base[t];
   const uint32_t u0 = j * per;
   uint32_t* row = lut + t * M;
   // Lane j owns slots u0 .. u0 + per - 1 but writes them starting at offset
@@ -497,44 +536,42 @@ __device__ __forceinline__ void build_lut_table(const LayerDev& L, uint32_t* lut
   // different banks (in order, every lane would hit the same bank: runs of
   // per = 32 slots are 128 bytes apart).  Both starting symbols are found
   // before the loop, so the wrap is a select, not a divergent search.
-  const uint32_t i0 = (uint32_t)j & (per - 1);
-  if (A == 0) {
+  const uint32_t i0 = j & (per - 1);
+  if (n == 0) {
     for (uint32_t k = 0; k < per; k++) row[u0 + ((i0 + k) & (per - 1))] = 0;
     return;
   }
-  // largest s with F_s <= u, for u = u0 + i0 and u = u0 (the two searches
+  // largest i with F_i <= u, for u = u0 + i0 and u = u0 (the two searches
   // advance together, their reads in flight at once)
-  uint32_t s_mid = 0, s_start = 0;
-  for (uint32_t n = A; n > 1;) {
-    const uint32_t h = n >> 1;
-    const uint32_t c_mid = cum[base + s_mid + h], c_start = cum[base + s_start + h];
-    if ((c_mid & 0xFFFF) <= u0 + i0) s_mid += h;
-    if ((c_start & 0xFFFF) <= u0) s_start += h;
-    n -= h;
+  uint32_t mid = 0, start = 0;
+  for (uint32_t w = n; w > 1;) {
+    const uint32_t h = w >> 1;
+    const uint32_t c_mid = sym[mid + h], c_start = sym[start + h];
+    if ((c_mid & 0x7FF) <= u0 + i0) mid += h;
+    if ((c_start & 0x7FF) <= u0) start += h;
+    w -= h;
   }
-  const int field = (t & 7) + 1;
-  const uint32_t e_mid = cum[base + s_mid], e_start = cum[base + s_start];
-  uint32_t s = s_mid, e = e_mid;
+  const int32_t mn = L.tab_min[t], zs = (t & 7) == 7 ? 1 : 0;
+  const uint32_t e_start = sym[start], n_start = sym[min(start + 1, n - 1)];
+  uint32_t i = mid, e = sym[mid], next = sym[min(mid + 1, n - 1)], base = 0, end = 0;
+  auto take = [&]() {   // the entry of slot u is base + (u << (12 or 11)) up to slot end
+    const uint32_t F = e & 0x7FF, f = ((e >> 11) & 0x7FF) + 1;
+    const uint32_t z = (uint32_t)(((int32_t)(e >> 22) + mn) << zs);
+    end = F + f;
+    base = WIDE ? (f - 1) + ((z & 0x3FF) << 22) - (F << 11) : f + ((z & 0xFF) << 24) - (F << 12);
+  };
+  take();
   for (uint32_t k = 0; k < per; k++) {
-    const uint32_t i = (i0 + k) & (per - 1);
-    const uint32_t u = u0 + i;
-    if (i == 0) {   // wrapped to the start of the run
-      s = s_start;
-      e = e_start;
+    const uint32_t o = (i0 + k) & (per - 1), u = u0 + o;
+    const bool wrap = o == 0 && k != 0;
+    if (wrap || u >= end) {
+      i = wrap ? start : i + 1;
+      e = wrap ? e_start : next;
+      next = wrap ? n_start : sym[min(i + 1, n - 1)];
+      take();
     }
-    while (s + 1 < A && (e & 0xFFFF) + (e >> 16) <= u) e = cum[base + ++s];
-    uint32_t F = e & 0xFFFF, f = e >> 16;
-    const int32_t v = (int32_t)s + L.tab_min[t];
-    const int32_t z = field < 8 ? v : 2 * v;
-    row[u] = WIDE ? (f - 1) | ((u - F) << 11) | ((uint32_t)(z & 0x3FF) << 22)
-                  : f | ((u - F) << 12) | ((uint32_t)(z & 0xFF) << 24);
+    row[u] = base + (u << (WIDE ? 11 : 12));
   }
-}
-
-template <bool WIDE>
-__device__ __forceinline__ void build_lut(const LayerDev& L, uint32_t* lut, const uint32_t* cum) {
-  for (int t = (int)wave_id(); t < 16; t += kWavesPerGroup)
-    build_lut_table<WIDE>(L, lut, cum, t, threadIdx.x & 63);
 }
 
 // LDS bytes of the payload rings of a workgroup (all waves, all halves).
@@ -2372,88 +2409,62 @@ __device__ __forceinline__ uint32_t ring_offset(const LayerDev& L) {
 // Each symbol writes the bucket starts inside its own slot range.
 //
 // Compact form (paths.h): the waves count their tables' symbols first, so that
-// every wave knows where its entries start and whether all fit.
+// every wave knows where its entries start and whether all fit.  Returns the
+// bits of its buckets, or 0.
 __device__ __forceinline__ uint32_t build_compact(const LayerDev& L, uint32_t* lds, uint32_t area) {
-  const int lane = threadIdx.x & 63, wave = (int)wave_id();
+  const uint32_t lane = threadIdx.x & 63, t = wave_id();
   uint32_t* const count = lds + area / 4;   // in the ring area
-  for (int t = wave; t < 16; t += kWavesPerGroup) {
-    const EP_GLOBAL uint16_t* f = gptr<const uint16_t>(L.blob + L.tab_off[t]);
-    const uint32_t A = L.tab_A[t];
-    uint32_t n = 0;
-    for (uint32_t s = lane; s < A; s += kWaveSize) n += f[s] != 0;
-#pragma unroll
-    for (int d = 1; d < kWaveSize; d <<= 1) n += __shfl_xor(n, d, kWaveSize);
-    if (lane == 0) count[t] = n;
-  }
+  const uint32_t mine = count_table(L);
+  if (lane == 0) count[t] = mine;
   __syncthreads();
-  uint32_t base[16], total = 0;
+  uint32_t at = 0, total = 0;   // where this wave's entries start; all entries
 #pragma unroll
-  for (int t = 0; t < 16; t++) {
-    base[t] = total;
-    total += uni(count[t]) + 1;
+  for (uint32_t q = 0; q < 16; q++) {
+    at = q == t ? total : at;
+    total += uni(count[q]) + 1;
   }
   const uint32_t need = 4 * (total + 2);   // two reads past the last entry
   const uint32_t k = need <= compact_buckets(area, kCompactBits) ? kCompactBits
                      : need <= compact_buckets(area, kCompactBitsLow) ? kCompactBitsLow : 0u;
   if (threadIdx.x == 0) lds[(area - kCompactTail) / 4] = k;
   if (k == 0) return 0;
-  uint16_t* const bk = reinterpret_cast<uint16_t*>(lds) + compact_buckets(area, k) / 2;
   const uint32_t sh = L.b > k ? L.b - k : 0, M = 1u << L.b;
-  for (int t = wave; t < 16; t += kWavesPerGroup) {
-    const EP_GLOBAL uint16_t* f = gptr<const uint16_t>(L.blob + L.tab_off[t]);
-    const uint32_t A = L.tab_A[t];
-    const int32_t mn = L.tab_min[t], zs = (t & 7) == 7 ? 1 : 0;   // field 8 stores 2m
-    uint32_t run = 0, at = base[0];
-#pragma unroll
-    for (int q = 1; q < 16; q++) at = t == q ? base[q] : at;
-    uint16_t* const row = bk + ((uint32_t)t << k);
-    for (uint32_t s0 = 0; s0 < A; s0 += kWaveSize) {
-      const uint32_t s = s0 + lane;
-      const uint32_t fs = s < A ? f[s] : 0u;
-      const uint64_t have = __ballot(fs != 0);
-      uint32_t incl = fs;
-#pragma unroll
-      for (int d = 1; d < kWaveSize; d <<= 1) {
-        const uint32_t o = __shfl_up(incl, d, kWaveSize);
-        if (lane >= d) incl += o;
-      }
-      if (fs) {
-        const uint32_t F = run + incl - fs;
-        const uint32_t i = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(have >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)have, 0u));
-        lds[i] = F | ((uint32_t)(((int32_t)s + mn) << zs) << 16);
-        for (uint32_t j = (F + (1u << sh) - 1) >> sh; j < (F + fs + (1u << sh) - 1) >> sh; j++) row[j] = (uint16_t)i;
-      }
-      run += __shfl(incl, kWaveSize - 1, kWaveSize);
-      at += (uint32_t)__builtin_popcountll(have);
-    }
-    if (lane == 0) lds[at] = M;
-    if (run == 0)   // no symbols: every bucket points at the end entry
-      for (uint32_t j = lane; j < (1u << k); j += kWaveSize) row[j] = (uint16_t)at;
-  }
+  const int32_t mn = L.tab_min[t], zs = (t & 7) == 7 ? 1 : 0;   // field 8 stores 2m
+  uint16_t* const row = reinterpret_cast<uint16_t*>(lds) + compact_buckets(area, k) / 2 + (t << k);
+  uint32_t sum = 0;
+  const uint32_t n = scan_table(L, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t i) {
+    if (!f) return;
+    lds[at + i] = F | ((uint32_t)(((int32_t)s + mn) << zs) << 16);
+    const uint32_t j1 = (F + f + (1u << sh) - 1) >> sh;
+    for (uint32_t j = (F + (1u << sh) - 1) >> sh; j < j1; j++) row[j] = (uint16_t)(at + i);
+  }, sum);
+  if (lane == 0) lds[at + n] = M;
+  if (sum == 0)   // no symbols: every bucket points at the end entry
+    for (uint32_t j = lane; j < (1u << k); j += kWaveSize) row[j] = (uint16_t)at;
   if (threadIdx.x < 2) lds[total + threadIdx.x] = M;
   return k;
 }
 
 __device__ __forceinline__ void build_search(const LayerDev& L, uint32_t* lds) {
   if (L.compact && build_compact(L, lds, search_area(L.b, L.sum_A, true))) return;
-  uint16_t* cum = reinterpret_cast<uint16_t*>(lds);
   const SearchLayout S = search_layout(L.b, L.sum_A);
-  uint16_t* bk = cum + S.bucket / 2;
+  const uint32_t lane = threadIdx.x & 63, t = wave_id();
   const uint32_t shift = L.b - S.bucket_bits, n1 = (1u << S.bucket_bits) + 1;
-  scan_tables(
-      L,
-      [&](int t, uint32_t s, uint32_t F, uint32_t f) {
-        cum[L.tab_base[t] + t + s] = (uint16_t)F;
-        const uint32_t j0 = (F + (1u << shift) - 1) >> shift, j1 = (F + f + (1u << shift) - 1) >> shift;
-        for (uint32_t j = j0; j < j1; j++) bk[t * n1 + j] = (uint16_t)s;
-      },
-      [&](int t, uint32_t M) {
-        cum[L.tab_base[t] + t + L.tab_A[t]] = (uint16_t)M;
-        bk[t * n1 + n1 - 1] = (uint16_t)(L.tab_A[t] ? L.tab_A[t] - 1 : 0);
-      });
+  uint16_t* const cum = reinterpret_cast<uint16_t*>(lds) + L.tab_base[t] + t;
+  uint16_t* const bk = reinterpret_cast<uint16_t*>(lds) + S.bucket / 2 + t * n1;
+  uint32_t sum = 0;
+  scan_table(L, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t) {
+    cum[s] = (uint16_t)F;
+    const uint32_t j0 = (F + (1u << shift) - 1) >> shift, j1 = (F + f + (1u << shift) - 1) >> shift;
+    for (uint32_t j = j0; j < j1; j++) bk[j] = (uint16_t)s;
+  }, sum);
+  if (lane == 0) {
+    cum[L.tab_A[t]] = (uint16_t)sum;
+    bk[n1 - 1] = (uint16_t)(L.tab_A[t] ? L.tab_A[t] - 1 : 0);
+  }
   if (threadIdx.x < 32) {
-    const uint32_t t = threadIdx.x & 15;
-    lds[S.meta / 4 + threadIdx.x] = threadIdx.x < 16 ? L.tab_base[t] + t : (uint32_t)L.tab_min[t];
+    const uint32_t q = threadIdx.x & 15;
+    lds[S.meta / 4 + threadIdx.x] = threadIdx.x < 16 ? L.tab_base[q] + q : (uint32_t)L.tab_min[q];
   }
 }
 
@@ -2466,14 +2477,12 @@ __device__ __forceinline__ uint32_t global_base(const LayerDev& L, uint32_t t) {
 }
 
 __device__ __forceinline__ void build_global(const LayerDev& L, uint32_t* lds) {
-  uint16_t* cum = reinterpret_cast<uint16_t*>(lds);
   const uint32_t g = L.g_bits, G = 1u << g;
-  scan_tables(
-      L,
-      [&](int t, uint32_t s, uint32_t F, uint32_t) {
-        if ((s & (G - 1)) == 0) cum[global_base(L, (uint32_t)t) + (s >> g)] = (uint16_t)F;
-      },
-      [](int, uint32_t) {});
+  uint16_t* const cum = reinterpret_cast<uint16_t*>(lds) + global_base(L, wave_id());
+  uint32_t sum = 0;
+  scan_table(L, [&](uint32_t s, uint32_t F, uint32_t, uint32_t) {
+    if ((s & (G - 1)) == 0) cum[s >> g] = (uint16_t)F;
+  }, sum);
   if (threadIdx.x < 64) {
     const uint32_t t = threadIdx.x & 15, q = threadIdx.x >> 4;
     lds[L.g_meta / 4 + threadIdx.x] = q == 0 ? global_base(L, t)
@@ -2483,30 +2492,42 @@ __device__ __forceinline__ void build_global(const LayerDev& L, uint32_t* lds) {
   }
 }
 
+// The slot tables are filled from the symbols that occur, collected in the ring
+// area: each table's where its index range would start, or, when the ranges
+// together are larger than the area, in a sixteenth of it (wide tables at 6 bits
+// per weight: ranges of 9,600 in all, 420 symbols in the largest table).
+template <bool WIDE>
+__device__ __forceinline__ void build_lut(const LayerDev& L, uint32_t* lds) {
+  constexpr uint32_t kRoom = kRingBytes / 4;
+  const uint32_t t = wave_id();
+  const bool ranges = uni(L.sum_A) <= kRoom;
+  uint32_t* const sym = lds + (16u << L.b) + (ranges ? uni(L.tab_base[t]) : t * (kRoom / 16));
+  const uint32_t room = ranges ? kRoom : kRoom / 16;
+  uint32_t sum = 0;
+  const uint32_t n = scan_table(L, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t i) {
+    if (f && i < room) sym[i] = F | ((f - 1) << 11) | (s << 22);
+  }, sum);
+  if (n <= room) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's own writes: no barrier
+    fill_lut_table<WIDE>(L, lds, sym, n);
+  } else {
+    // more symbols than the room holds: every lane fills the slot range of its own
+    // symbol straight from the prefix sums
+    uint32_t* const row = lds + (t << L.b);
+    const int32_t mn = L.tab_min[t], zs = (t & 7) == 7 ? 1 : 0;
+    scan_table(L, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t) {
+      const uint32_t z = (uint32_t)(((int32_t)s + mn) << zs);
+      for (uint32_t i = 0; i < f; i++)
+        row[F + i] = WIDE ? (f - 1) | (i << 11) | ((z & 0x3FF) << 22) : f | (i << 12) | ((z & 0xFF) << 24);
+    }, sum);
+  }
+}
+
 template <int PATH>
 __device__ __forceinline__ void build_tables(const LayerDev& L, uint32_t* lds) {
-  if (PATH == kPathGlobal) {
-    build_global(L, lds);
-  } else if (PATH != kPathSearch && L.sum_A <= kRingBytes / 4) {
-    uint32_t* cum = lds + (16u << L.b);   // scratch inside the ring area
-    build_cumulative(L, cum);
-    __syncthreads();
-    build_lut<PATH == kPathWide>(L, lds, cum);
-  } else if (PATH != kPathSearch) {
-    // more symbols than the scratch holds (wide tables): every lane fills the
-    // slot range of its own symbol straight from the table's prefix scan
-    scan_tables(L, [&](int t, uint32_t s, uint32_t F, uint32_t f) {
-      uint32_t* row = lds + ((uint32_t)t << L.b);
-      const int field = (t & 7) + 1;
-      const int32_t v = (int32_t)s + L.tab_min[t];
-      const uint32_t z = (uint32_t)(field < 8 ? v : 2 * v);
-      for (uint32_t i = 0; i < f; i++)
-        row[F + i] = PATH == kPathWide ? (f - 1) | (i << 11) | ((z & 0x3FF) << 22)
-                                       : f | (i << 12) | ((z & 0xFF) << 24);
-    }, [](int, uint32_t) {});
-  } else {
-    build_search(L, lds);
-  }
+  if constexpr (PATH == kPathGlobal) build_global(L, lds);
+  else if constexpr (PATH == kPathSearch) build_search(L, lds);
+  else build_lut<PATH == kPathWide>(L, lds);
 }
 
 // A wave task is four tiles (two chains of two).  When all four are full (V
@@ -2633,19 +2654,42 @@ __device__ __forceinline__ void run_segment(const LayerDev& L, uint32_t* lds, ui
 // the kernel family of its own layer (the path is uniform over the workgroup).
 constexpr int kPathMixed = 15;
 
+// Last layer of the list whose `key` (ascending, 0 first) is at most v: the
+// lanes read 64 descriptors at once, where a walk would wait for each in turn.
+__device__ __forceinline__ int find_layer(const LayerDev* layers, int n_layers, uint32_t LayerDev::*key,
+                                          uint32_t v) {
+  const int lane = threadIdx.x & 63;
+  int found = 0;
+  for (int l0 = 0; l0 < n_layers; l0 += kWaveSize) {
+    const uint32_t k = l0 + lane < n_layers ? *gptr<const uint32_t>(&(layers[l0 + lane].*key)) : ~0u;
+    const uint64_t at_most = __ballot(l0 + lane < n_layers && k <= v);
+    found += __builtin_popcountll(at_most);
+    if (~at_most) break;
+  }
+  return found - 1;
+}
+
 // Decode global tasks [t_begin, t_end) of a layer list: per layer segment the
 // workgroup builds that layer's tables, then its waves take tasks in turn.
-// DOT: the fused product (every layer's output mode is kOutDotI8).
+// per_group: the tasks of a workgroup, or 0 when each belongs to one layer
+// (LayerDev::wg_begin).  DOT: the fused product (every layer's output mode is
+// kOutDotI8).
 template <int PATH, bool DOT = false>
 __device__ __forceinline__ void run_layers(const LayerDev* layers, int n_layers, uint32_t total,
                            uint32_t per_group, int32_t* status) {
   extern __shared__ uint32_t lds[];
   saturate_conversions();
-  const uint32_t t_begin = blockIdx.x * per_group;
-  const uint32_t t_end = min(total, t_begin + per_group);
-  if (t_begin >= t_end) return;
+  uint32_t t_begin = blockIdx.x * per_group, t_end = min(total, t_begin + per_group);
   int li = 0;
-  while (li + 1 < n_layers && layers[li + 1].task_begin <= t_begin) li++;
+  if (n_layers > 1) li = uni(find_layer(layers, n_layers, per_group ? &LayerDev::task_begin : &LayerDev::wg_begin,
+                                        per_group ? t_begin : blockIdx.x));
+  if (per_group == 0) {
+    const LayerDev& L = layers[li];
+    const uint32_t first = (blockIdx.x - L.wg_begin) * L.wg_tasks;
+    t_begin = uni(L.task_begin + first);
+    t_end = uni(L.task_begin + min(L.n_tasks, first + L.wg_tasks));
+  }
+  if (t_begin >= t_end) return;
   for (uint32_t seg = t_begin; seg < t_end && li < n_layers; li++) {
     const LayerDev& L = layers[li];
     const uint32_t seg_end = min(t_end, L.task_begin + L.n_tasks);
