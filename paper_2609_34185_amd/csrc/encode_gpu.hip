@@ -143,42 +143,135 @@ __global__ __launch_bounds__(kFetchThreads) void k_prep_mu(const float* x, int64
   }
 }
 
-// One thread per vector: fields at scale s, table extents.
-__global__ __launch_bounds__(256) void k_quantize(const float* x, const double* mu,
-                                                  const int64_t* rows, int64_t nrows, int64_t cvec,
-                                                  int64_t C, double s, int32_t* fl, int32_t* lohi) {
-  __shared__ int32_t s_lo[16], s_hi[16];
-  const int t = threadIdx.x;
-  if (t < 16) {
-    s_lo[t] = INT_MAX;
-    s_hi[t] = INT_MIN;
-  }
-  __syncthreads();
-  const int64_t id = (int64_t)blockIdx.x * 256 + t;
-  if (id < nrows * cvec) {
-    const int64_t k = id / cvec, jv = id - k * cvec;
-    const int64_t r = rows ? rows[k] : k;
-    const float4* xv = reinterpret_cast<const float4*>(x + r * C + 8 * jv);
-    const float4 a = xv[0], b = xv[1];
-    const float xs[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    const double m = mu[r];
-    double y[8];
-    for (int j = 0; j < 8; j++) y[j] = ((double)xs[j] / m) / s;
-    int32_t p2[8], f[9];
-    em::e8_point(y, p2);
-    em::split_fields(p2, f);
-    int32_t* o = fl + 9 * id;
-    for (int i = 0; i < 9; i++) o[i] = f[i];
-    for (int i = 1; i <= 8; i++) {
-      const int ti = em::table_index(i, f[0]) - 1;
-      atomicMin(&s_lo[ti], f[i]);
-      atomicMax(&s_hi[ti], f[i]);
+// Nearest E8 point and field tuple of one vector (em::e8_point, em::split_fields,
+// operation for operation), with every array indexed by constants so that all of
+// it stays in registers: the shared source's moved coordinate z[k] and its choice
+// between two candidate arrays put them in scratch memory here.
+__device__ __forceinline__ void d8_registers(const double (&y)[8], double (&z)[8]) {
+  double r[8], tot = 0, best = 0;
+  int k = 0;
+#pragma unroll
+  for (int j = 0; j < 8; j++) {
+    z[j] = __builtin_rint(y[j]);
+    r[j] = y[j] - z[j];
+    tot += z[j];
+    const double a = __builtin_fabs(r[j]);
+    if (j == 0) {
+      best = a;
+    } else if (a > best) {
+      best = a;
+      k = j;
     }
   }
+  // odd sum (an integer; half of one is a half-integer): fmod(|tot|, 2) == 1
+  const double h = 0.5 * tot;
+  const bool odd = __builtin_fabs(h - __builtin_rint(h)) == 0.5;
+#pragma unroll
+  for (int j = 0; j < 8; j++) z[j] = odd && j == k ? z[j] + (r[j] < 0 ? -1.0 : 1.0) : z[j];
+}
+
+__device__ __forceinline__ void e8_fields(const double (&y)[8], int32_t (&f)[9]) {
+  double a[8], h[8], yh[8], da = 0, dh = 0;
+#pragma unroll
+  for (int j = 0; j < 8; j++) yh[j] = y[j] - 0.5;
+  d8_registers(y, a);
+  d8_registers(yh, h);
+#pragma unroll
+  for (int j = 0; j < 8; j++) {
+    h[j] += 0.5;
+    dh += (y[j] - h[j]) * (y[j] - h[j]);
+    da += (y[j] - a[j]) * (y[j] - a[j]);
+  }
+  const bool half = dh < da;
+  int32_t p2[8], par = 0;
+#pragma unroll
+  for (int j = 0; j < 8; j++) p2[j] = (int32_t)(2.0 * (half ? h[j] : a[j]));
+  const int32_t c = p2[0] & 1;
+  f[0] = c;
+#pragma unroll
+  for (int j = 0; j < 7; j++) {
+    f[1 + j] = (p2[j] - c) >> 1;
+    par += f[1 + j];
+  }
+  f[8] = (((p2[7] - c) >> 1) - (par & 1)) >> 1;
+}
+
+// Minimum over the wave's lanes, in lane 63 (DPP moves).
+__device__ __forceinline__ int32_t wave_min(int32_t v) {
+  constexpr int kMax = INT_MAX;
+  v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x111, 0xF, 0xF, false));   // row_shr:1
+  v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x112, 0xF, 0xF, false));   // row_shr:2
+  v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x114, 0xF, 0xF, false));   // row_shr:4
+  v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x118, 0xF, 0xF, false));   // row_shr:8
+  v = min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x142, 0xA, 0xF, false));   // row_bcast:15
+  return min(v, __builtin_amdgcn_update_dpp(kMax, v, 0x143, 0xC, 0xF, false));   // row_bcast:31
+}
+
+// Fields of vectors at scale s, and table extents: one thread per vector, a
+// block taking groups of 256 vectors in turn (quantize_blocks).  Each lane keeps the
+// extents of the 16 field tables over its vectors (hi as the minimum of ~f),
+// which are reduced over the wave once at the end -- sixteen LDS atomics a vector,
+// on addresses shared by the whole block, took most of the time -- and the fields
+// go out through LDS, whole lines at a time.  An encode of 5120 x 17408 (twelve
+// search steps over 2^18 vectors and one full pass): 11.05 -> 10.15 ms.
+constexpr int kQuantizeThreads = 256;
+__global__ __launch_bounds__(kQuantizeThreads) void k_quantize(const float* x, const double* mu,
+                                                               const int64_t* rows, int64_t nrows,
+                                                               int64_t cvec, int64_t C, double s,
+                                                               int32_t* fl, int32_t* lohi) {
+  __shared__ int32_t s_f[9 * kQuantizeThreads];
+  __shared__ int32_t s_lo[32];   // per coset and field: lo, then ~hi
+  const int t = threadIdx.x;
+  if (t < 32) s_lo[t] = INT_MAX;
+  int32_t lo[2][8], nhi[2][8];
+#pragma unroll
+  for (int i = 0; i < 8; i++) lo[0][i] = lo[1][i] = nhi[0][i] = nhi[1][i] = INT_MAX;
+  const int64_t n = nrows * cvec;
+  for (int64_t id0 = (int64_t)blockIdx.x * kQuantizeThreads; id0 < n; id0 += (int64_t)gridDim.x * kQuantizeThreads) {
+    const int64_t id = id0 + t;
+    if (id < n) {
+      const int64_t k = id / cvec, jv = id - k * cvec;
+      const int64_t r = rows ? rows[k] : k;
+      const float4* xv = reinterpret_cast<const float4*>(x + r * C + 8 * jv);
+      const float4 a = xv[0], b = xv[1];
+      const double m = mu[r];
+      const double y[8] = {((double)a.x / m) / s, ((double)a.y / m) / s, ((double)a.z / m) / s,
+                           ((double)a.w / m) / s, ((double)b.x / m) / s, ((double)b.y / m) / s,
+                           ((double)b.z / m) / s, ((double)b.w / m) / s};
+      int32_t f[9];
+      e8_fields(y, f);
+#pragma unroll
+      for (int i = 0; i < 9; i++) s_f[9 * t + i] = f[i];
+#pragma unroll
+      for (int i = 0; i < 8; i++) {
+        const int32_t v = f[1 + i];
+        lo[0][i] = min(lo[0][i], f[0] ? INT_MAX : v);
+        lo[1][i] = min(lo[1][i], f[0] ? v : INT_MAX);
+        nhi[0][i] = min(nhi[0][i], f[0] ? INT_MAX : ~v);
+        nhi[1][i] = min(nhi[1][i], f[0] ? ~v : INT_MAX);
+      }
+    }
+    __syncthreads();
+    const int64_t left = 9 * (n - id0);
+    const int count = left < 9 * kQuantizeThreads ? (int)left : 9 * kQuantizeThreads;
+    for (int i = t; i < count; i += kQuantizeThreads) fl[9 * id0 + i] = s_f[i];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int c = 0; c < 2; c++)
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      const int32_t a = wave_min(lo[c][i]), b = wave_min(nhi[c][i]);
+      if ((t & 63) == 63) {
+        atomicMin(&s_lo[8 * c + i], a);
+        atomicMin(&s_lo[16 + 8 * c + i], b);
+      }
+    }
   __syncthreads();
-  if (t < 16 && s_lo[t] <= s_hi[t]) {
+  // table 1 + 8 c + i; ~hi is INT_MAX where no vector of the coset was seen
+  if (t < 16 && s_lo[t] != INT_MAX) {
     atomicMin(&lohi[2 * (t + 1)], s_lo[t]);
-    atomicMax(&lohi[2 * (t + 1) + 1], s_hi[t]);
+    atomicMax(&lohi[2 * (t + 1) + 1], ~s_lo[16 + t]);
   }
 }
 
@@ -497,6 +590,13 @@ __global__ __launch_bounds__(256) void k_select(const int32_t* cand, uint64_t ca
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
+// Blocks of k_quantize: one group of vectors each up to eight blocks a CU (the
+// search steps' samples), then more groups each, so that the extents are reduced
+// once per wave and not per group.
+unsigned quantize_blocks(int64_t nv) {
+  return (unsigned)std::min<int64_t>((nv + kQuantizeThreads - 1) / kQuantizeThreads, 2048);
+}
+
 // Two pinned host buffers through which large device-to-host copies are
 // staged: a copy into pageable memory runs at a few GB/s, while a pinned one
 // runs at the link's rate and, chunk by chunk, overlaps the host copy of the
@@ -739,7 +839,7 @@ int quantize(Ctx* c, const int64_t* rows, int64_t nrows, double s, int32_t* lohi
     init[2 * i + 1] = INT_MIN;
   }
   EP_GTRY(c->to_dev(c->lohi, init, sizeof(init), "ep_encode_gpu: copy"));
-  hipLaunchKernelGGL(k_quantize, dim3(blocks_for(nv, 256)), dim3(256), 0, c->st, c->x, c->mu,
+  hipLaunchKernelGGL(k_quantize, dim3(quantize_blocks(nv)), dim3(kQuantizeThreads), 0, c->st, c->x, c->mu,
                      rows ? c->rows : nullptr, nrows, c->cvec, c->C, s, dst, c->lohi);
   EP_LAUNCHED("ep_encode_gpu: launch (quantize)");
   return c->to_host(lohi, c->lohi, sizeof(init), "ep_encode_gpu: quantize");
@@ -892,7 +992,7 @@ int cand_quantize(Ctx* c, int k, double s, int32_t* lohi) {
   init_lohi(init);
   EP_GTRY(c->to_dev(c->lohi, init, sizeof(init), "ep_encode_gpu: copy"));
   const int64_t nv = c->R * c->cvec;
-  hipLaunchKernelGGL(k_quantize, dim3(blocks_for(nv, 256)), dim3(256), 0, c->st, c->x, c->mu,
+  hipLaunchKernelGGL(k_quantize, dim3(quantize_blocks(nv)), dim3(kQuantizeThreads), 0, c->st, c->x, c->mu,
                      nullptr, c->R, c->cvec, c->C, s, cand_ptr(c, k), c->lohi);
   EP_LAUNCHED("ep_encode_gpu: launch (candidate quantize)");
   return c->to_host(lohi, c->lohi, sizeof(init), "ep_encode_gpu: candidate quantize");
