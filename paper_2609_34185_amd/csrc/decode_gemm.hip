@@ -17,7 +17,7 @@ typedef __bf16 v8bf_t __attribute__((ext_vector_type(8)));
 // once per block and each slab fragment once per item; items are dealt to the
 // waves, and when there are fewer items than waves K is split over the idle
 // waves, whose partial sums meet in the ring area of the LDS (idle between two
-// blocks' decodes), two result tiles at a time, and are added in slice order by
+// blocks' decodes), two result tiles at a time, and are added in a fixed order by
 // all threads: no atomics on Y, and nothing to clear before the launch.  NT and XT
 // are template arguments so that no load is issued for a tile the block does
 // not have.  MFMA operands: lane l supplies row l mod 16 of an X tile and of a
@@ -159,9 +159,15 @@ __device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmAr
     __syncthreads();
     for (uint32_t e = threadIdx.x; e < I * np * 64; e += kThreads) {
       const uint32_t l = e & 63, ip = e >> 6, p = ip % np, it = ip / np;   // lane, pair member, item
-      Acc sum{0, 0, 0, 0};
-      for (uint32_t sl = 0; sl < S; sl++)
-        sum += *reinterpret_cast<const Acc*>(scratch + (2 * (sl * I + it) + p) * 1024 + 16 * l);
+      // four chains of every fourth slice: at most five roundings a sum instead of 15,
+      // and independent LDS reads
+      Acc part[4] = {};
+      for (uint32_t s0 = 0; s0 < S; s0 += 4)
+#pragma unroll
+        for (uint32_t j = 0; j < 4; j++)
+          if (s0 + j < S)
+            part[j] += *reinterpret_cast<const Acc*>(scratch + (2 * ((s0 + j) * I + it) + p) * 1024 + 16 * l);
+      const Acc sum = (part[0] + part[1]) + (part[2] + part[3]);
       const uint32_t x = (p0 + p) / NT, c = (p0 + p) % NT;
 #pragma unroll
       for (uint32_t r = 0; r < 4; r++) put(16 * (XT * it + x) + 4 * (l >> 4) + r, 16 * c + (l & 15), sum[r]);
