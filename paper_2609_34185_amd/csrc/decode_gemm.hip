@@ -130,7 +130,9 @@ __device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmAr
     if (t < m && rl < RB && row0 + rl < L.rows) y[(uint64_t)t * L.rows + row0 + rl] = v;
   };
   if (S == 1) {
-    for (uint32_t it = it0; it < I; it += kWavesPerGroup) {
+    // 9 to 15 items leave waves I..15 idle: their it0 is another wave's item, with no K
+    // left to them, so they must store nothing
+    for (uint32_t it = busy ? it0 : I; it < I; it += kWavesPerGroup) {
       Acc acc[XT][NT];
       product(it, acc);
 #pragma unroll

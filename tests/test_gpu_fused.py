@@ -386,3 +386,35 @@ def test_fused_bf16_product_rejects_bad_arguments(E, oracle):
     # the INT8 product refuses a tensor outside the INT8 container; the BF16 one takes it
     assert lib.ep_decode_gemm_i8(E.C.byref(info), d_blob.data_ptr(), x.data_ptr(), 20, y.data_ptr(),
                                  None, d_ws.data_ptr(), ws, None, None) == E.ERR_UNSUPPORTED
+
+
+# ---- work items of the MFMA products against the sixteen waves ------------------------
+# rows of W', slab tiles of a block on 256 CUs, X tiles of a work item
+ITEM_SHAPES = [(300, 1, 4), (5000, 2, 2), (9000, 3, 2), (16000, 4, 1)]
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["int8", "bf16"])
+@pytest.mark.parametrize("cols", [64, 712])
+@pytest.mark.parametrize("rows,nt,xt", ITEM_SHAPES, ids=[f"slab_tiles_{s[1]}" for s in ITEM_SHAPES])
+def test_fused_product_work_items(E, oracle, rows, nt, xt, cols, bf16):
+    """8, 9, 15 and 16 work items a block for every shape of the product: K split in two, one
+    item a wave with seven waves idle, with one idle, and with none.  K of one 64-byte step,
+    where an idle wave's stores would come last, and of several slices; Y starts as garbage."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus != 256 or (-(-rows // cus) + 15) // 16 == nt
+    w = W.ragged_tensor(80 + nt, rows, cols, scale=0.05)
+    blob, _ = E.encode(w, 4.0) if bf16 else E.encode(w, 6.0, container=E.CONT_INT8_ROW)
+    wref, _ = oracle.decode(blob, oracle.BF16 if bf16 else oracle.INT8)
+    for items in (8, 9, 15, 16):
+        m = 16 * xt * (items - 1) + (1 if items % 2 else 16 * xt)
+        say(f"  work items: {rows} x {cols}, {items} items, m = {m}, bf16 = {bf16}")
+        if bf16:
+            xbits = bf16_activations(400 + items, m, cols)
+            y, _, st = fused_bf16(E, blob, xbits)
+            check_bf16_product(oracle, blob, xbits, y)
+        else:
+            x = activations(400 + items, m, cols)
+            y, _, st = fused_mfma(E, blob, x)
+            exact = torch.from_numpy(x).double() @ torch.from_numpy(wref).double().T   # below 2^53: exact
+            assert np.array_equal(y, exact.numpy().astype(np.int32))
+        assert st == 0
