@@ -58,10 +58,11 @@ uint32_t lds_bytes(uint32_t path, const ep_tensor_info& I) {
 // Whether the weights need a clamp before the conversion to the output type.
 // The conversions to FP16 and FP8 saturate by themselves for finite FP32
 // inputs (saturate_conversions), so only weights that may be infinite in FP32
-// (ep_blob_info caps its bound at 3e38) need one; BF16's range ends below FP32's.
+// need one; BF16 rounds to infinity above 3.39e38.  ep_blob_info caps its bound
+// at 3e38: a tensor at the cap may hold weights of either kind.
 bool needs_clamp(int dt, float max_abs_weight) {
   switch (dt) {
-    case EP_BF16: return max_abs_weight >= 3.38953139e38f;
+    case EP_BF16:
     case EP_FP16:
     case EP_FP8_E4M3:
     case EP_FP8_E5M2: return max_abs_weight >= 3.0e38f;

@@ -2341,8 +2341,8 @@ __device__ __forceinline__ void lut_task_rows(const Hot& L, uint8_t* lds, uint32
 // entries).  ONLY: the one output type of the kernel, never streamed (the fused
 // MFMA products read their slab back), or kAnyType.  Returns false for the
 // combinations the steady state does not cover (they take the generic loop).
-// The explicit clamp has instances only for the types whose conversion it may
-// be needed for, and neither it nor the rarer outputs have streaming ones.
+// The explicit clamp has instances for FP16 and FP8 (BF16's takes the generic
+// loop), and neither it nor the rarer outputs have streaming ones.
 template <int B, bool WIDE, bool DOT = false, int ONLY = kAnyType>
 __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
                                              uint32_t t0, int32_t* status) {
@@ -2352,6 +2352,7 @@ __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_
     lut_task_rows<B, kOutDotI8, false, WIDE>(L, lds, ring_area, t0, status);
     return true;
   } else if constexpr (ONLY != kAnyType) {
+    if (ONLY == EP_BF16 && L.saturate) return false;
     lut_task_rows<B, ONLY, false, WIDE>(L, lds, ring_area, t0, status);
     return true;
   } else {
@@ -2361,7 +2362,10 @@ __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_
       else lut_task_rows<B, DT, false, WIDE>(L, lds, ring_area, t0, status);
     };
     switch (L.out_dtype) {
-      case EP_BF16: plain(std::integral_constant<int, EP_BF16>{}); return true;
+      case EP_BF16:
+        if (L.saturate) return false;
+        plain(std::integral_constant<int, EP_BF16>{});
+        return true;
       case EP_FP16:
         if (L.saturate) lut_task_rows<B, EP_FP16, true, WIDE>(L, lds, ring_area, t0, status);
         else plain(std::integral_constant<int, EP_FP16>{});

@@ -336,6 +336,40 @@ def test_saturation(E, oracle, tasks):
         check_blob(E, oracle, blob, dtypes=["E5M2"], tag=f"sat e5m2 {tasks}")
 
 
+def scale_rows(E, blob, scales):
+    """The blob with the scales of its first rows replaced (its symbols stay as they are)."""
+    b = np.array(blob)
+    at = E.blob_info(b).off_sigma
+    b[at:at + 4 * len(scales)] = np.asarray(scales, np.float32).view(np.uint8)
+    return b
+
+
+# just above BF16's range and below FP32's, twice that, and past FP32's
+HUGE_SCALES = [3.395e38, 1.7e38, 1e38, 3e38]
+
+
+@pytest.mark.parametrize("tasks", TASKS)
+@pytest.mark.parametrize("case", ["full_tiles", "short_rows", "ragged", "wide", "search", "global"])
+def test_weights_beyond_the_finite_range(E, oracle, case, tasks):
+    """Rows whose weights leave the range of BF16 or of FP32 decode to the largest finite value
+    of every 16- and 8-bit type, on every path and form of task."""
+    shape, target, kw = {"full_tiles": ((72, 8 * 1024), 4.0, {}), "short_rows": ((300, 264), 4.0, {}),
+                         "ragged": ((200, 520), 4.0, dict(tile_vectors=77)), "wide": ((64, 4096), 6.6, {}),
+                         "search": ((64, 4096), 4.0, dict(prob_bits=12)), "global": ((40, 1024), 4.0, {})}[case]
+    w = W.ragged_tensor(90, *shape)
+    if case == "wide":
+        w[9, 32] += 3 << 7   # eight times as large (BF16 bits)
+    blob, _ = oracle.encode(w, target, **kw)
+    blob = scale_rows(E, blob, HUGE_SCALES)
+    info = E.blob_info(blob)
+    assert info.max_abs_weight == np.float32(3.0e38)
+    assert info.path == {"wide": 3, "search": 2}.get(case, 1)
+    assert np.isinf(oracle.decode(blob, oracle.FP32)[0][:4]).any()
+    with task_mode(tasks):
+        check_blob(E, oracle, blob, dtypes=["BF16", "FP16", "FP8", "E5M2", "FP32", "INT8", "UINT8"],
+                   tag=f"huge {case} {tasks}", path=4 if case == "global" else None)
+
+
 @pytest.mark.parametrize("shape,target,kw", [
     ((96, 8 * 1000), 4.0, {}),                        # full tasks, slot-table steady state
     ((64, 8 * 640), 7.0, {}),                         # larger coordinates

@@ -365,6 +365,24 @@ def test_fused_bf16_product_dit_layer(E, oracle):
         check_bf16_product(oracle, blob, xbits, y)
 
 
+@pytest.mark.parametrize("prob_bits", [11, 12], ids=["slot_table", "search"])
+def test_fused_bf16_product_saturates_weights(E, oracle, prob_bits):
+    """Weights beyond the BF16 range enter the product as the largest finite value: X of one-hot
+    rows reads single weights back, where an infinity anywhere in the row would give NaN."""
+    blob, _ = oracle.encode(W.ragged_tensor(91, 48, 8 * 600), 4.0, prob_bits=prob_bits)
+    blob = np.array(blob)
+    info = E.blob_info(blob)
+    blob[info.off_sigma:info.off_sigma + 16] = np.array([3.395e38, 1.7e38, 1e38, 3e38], np.float32).view(np.uint8)
+    w = bf16_values(oracle.decode(blob, oracle.BF16)[0])
+    assert np.isinf(oracle.decode(blob, oracle.FP32)[0][:4]).any() and np.isfinite(w).all()
+    cols = np.arange(20) * 239
+    x = np.zeros((20, info.cols), np.float32)
+    x[np.arange(20), cols] = 1.0
+    y, _, st = fused_bf16(E, blob, bf16_bits(x))
+    assert st == 0
+    assert np.array_equal(y.astype(np.float64), w[:, cols].T)
+
+
 def test_fused_bf16_product_rejects_bad_arguments(E, oracle):
     w = W.ragged_tensor(69, 32, 256)
     blob, _ = oracle.encode(w, 4.0)
