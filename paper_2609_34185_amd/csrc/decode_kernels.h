@@ -1342,8 +1342,8 @@ __device__ __forceinline__ void decode_task_fast(const Hot& L, uint8_t* lds, uin
       EP_REFILL_BOTH_W(WORK)                                                             \
       : EP_STEP_OUTS, [e0] "=&v"(e0), [e1] "=&v"(e1), [y0] "=&v"(y0), [y1] "=&v"(y1)     \
       : [cb0] "v"(cb0), [cb1] "v"(cb1), [off] "i"((FIELD - 1) * (4 << B)), [sg0] "v"(sg0), \
-        [sg1] "v"(sg1), [hc0] "v"(hc0), [hc1] "v"(hc1), [m] "s"(m), [nm] "v"(-m),        \
-        [X0] "v"(X0), [X1] "v"(X1), [bit] "s"(zbit), EP_STEP_INS                         \
+        [sg1] "v"(sg1), [hc0] "v"(hc0), [hc1] "v"(hc1), [m] "s"(hi), [nm] "v"(lo),       \
+        [X0] "v"(X0), [X1] "v"(X1), [bit] "s"(bit), EP_STEP_INS                          \
       : EP_STEP_CLOBBERS)
 
 template <int B, int FIELD, int YM, bool WIDE>
@@ -1353,7 +1353,10 @@ __device__ __forceinline__ void field_step2(uint32_t& x0, uint32_t& x1, uint32_t
                                             uint32_t X0, uint32_t X1, float m, FastChain& F0,
                                             FastChain& F1, uint32_t vH, uint32_t vrb0, uint32_t vrb1) {
   EP_STEP_TEMPS;
-  const uint32_t zbit = 1u << (WIDE ? 22 : 24);   // low bit of the entry's z
+  // operands that the step does not use stand for others that are in registers anyway: constants
+  // of their own were rebuilt three times a round
+  const uint32_t bit = FIELD == 8 ? 1u << (WIDE ? 22 : 24) : kStateLow;   // low bit of the entry's z
+  const float hi = YM == 2 ? m : __uint_as_float(kStateLow), lo = YM == 2 ? -m : sg0;
   if constexpr (WIDE) {
     if constexpr (YM == 0) EP_FIELD_ASM(EP_DEC_WIDE(0), EP_DEC_WIDE(1), "");
     else if constexpr (FIELD == 8 && YM == 1) EP_FIELD_ASM(EP_DEC_WIDE(0), EP_DEC_WIDE(1), EP_Y_PAR EP_Y_CVT_WIDE);
@@ -1727,8 +1730,9 @@ __device__ __forceinline__ void q_put(EP_GLOBAL uint8_t* base, uint32_t off, con
     put(reinterpret_cast<EP_GLOBAL u32x2*>(base + off), u32x2{a.w[0], a.w[1]});
   } else {
     EP_GLOBAL u32x4* o = reinterpret_cast<EP_GLOBAL u32x4*>(base + off);
-    put(o, u32x4{a.w[0], a.w[1], a.w[2], a.w[3]});
-    put(o + 1, u32x4{a.w[4], a.w[5], a.w[6], a.w[7]});
+    static_assert(!STREAM, "two stores a lane: see lut_task_any");
+    o[0] = u32x4{a.w[0], a.w[1], a.w[2], a.w[3]};
+    o[1] = u32x4{a.w[4], a.w[5], a.w[6], a.w[7]};
   }
 }
 
@@ -2342,7 +2346,10 @@ __device__ __forceinline__ void lut_task_rows(const Hot& L, uint8_t* lds, uint32
 // MFMA products read their slab back), or kAnyType.  Returns false for the
 // combinations the steady state does not cover (they take the generic loop).
 // The explicit clamp has instances for FP16 and FP8 (BF16's takes the generic
-// loop), and neither it nor the rarer outputs have streaming ones.
+// loop), and neither it nor the rarer outputs have streaming ones.  Nor has FP32,
+// where a lane stores a vector's 32 bytes as two halves: a diffusion-transformer block
+// (0.55 GB) takes 181 us, 273 with its output streamed and 239 with its payload too;
+// 17408 x 5120 at 2.5 bits per weight 120, 183 and 161, at 4 bits 133, 180 and 126.
 template <int B, bool WIDE, bool DOT = false, int ONLY = kAnyType>
 __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_t ring_area,
                                              uint32_t t0, int32_t* status) {
@@ -2380,7 +2387,7 @@ __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_
         return true;
       case EP_INT8: plain(std::integral_constant<int, EP_INT8>{}); return true;
       case EP_UINT8: lut_task_rows<B, EP_UINT8, false, WIDE>(L, lds, ring_area, t0, status); return true;
-      case EP_FP32: plain(std::integral_constant<int, EP_FP32>{}); return true;
+      case EP_FP32: lut_task_rows<B, EP_FP32, false, WIDE>(L, lds, ring_area, t0, status); return true;
       case EP_COORD2_I32: lut_task_rows<B, EP_COORD2_I32, false, WIDE>(L, lds, ring_area, t0, status); return true;
       default: return false;
     }
