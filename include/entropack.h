@@ -210,10 +210,13 @@ int ep_blob_info(const void* host_blob, uint64_t n, ep_tensor_info* info);
  * (two interleaved rANS chains, each over two tiles).  A launch with fewer than
  * 2048 such tasks whose layers all take the same slot-table path at b = 11, or the
  * search path with tables certain to fit its compact form, runs two-tile tasks
- * instead (one chain per wave): small layers then spread over twice as many waves.  The environment variable EP_SMALL_TASK_LIMIT, read at
- * each call, replaces the 2048 (0: always four-tile tasks).  The outputs do
- * not depend on the choice.  A launch that moves more than 256 MiB (payload and
- * weights) reads and writes past the caches. */
+ * instead (one chain per wave): small layers then spread over twice as many
+ * waves.  The environment variable EP_SMALL_TASK_LIMIT, read at each call,
+ * replaces the 2048 (0: always four-tile tasks).  The outputs do not depend on
+ * the choice.  A launch that moves more than 256 MiB (payload and weights) stores
+ * past the caches, and reads its payload past them when that is above 96 MiB,
+ * where a layer takes four-tile tasks of a slot-table path at b = 11 and is decoded to
+ * BF16, FP16, FP8 E4M3 or INT8. */
 /* Decode tiles [tile_begin, tile_end) of one tensor (Section 3.7: eq.
  * rans_decode, eq. point_inverse, eq. recon).  d_out receives R x C
  * elements of out_dtype (row-major); only the elements of the given tiles are

@@ -316,25 +316,39 @@ void use_small_tasks(std::vector<LayerDev>& D, uint32_t& total) {
 }
 
 // A launch that moves more bytes (payload in, weights out) than the last-level
-// cache holds cannot leave its output there for a reader, nor find its payload
-// there the next time: its four-tile steady state then streams both past the
-// caches.  Payload loads return behind a wave's older stores, and streaming
-// stores finish sooner.  With three sets in turn (cold caches): MLP set to FP8
-// (0.40 GB a launch) 180.5 -> 174.1 us, eight DiT blocks to BF16 (2.5 GB) 700 ->
-// 670 us.  Below the limit the reader gains more: an INT8 down projection (0.16
-// GB) followed by its product loses 5 us when its weights are streamed, and two
-// DiT blocks decoded again and again lose 15 us when their payload is.
-constexpr uint64_t kCacheBytes = 256ull << 20;
+// cache holds cannot leave all its output there for a reader: the four-tile slot-table
+// steady state then stores its weights past the caches, which finishes sooner and
+// leaves the payload cached for the next pass.  A payload that several such sets
+// decoded in turn would push out is read past the caches as well.  Diffusion-transformer
+// blocks (38 MB of payload and 275 MB of BF16 each), us a pass with no streaming / output /
+// both:
+//   blocks              one set again and again    three sets in turn
+//   1                   117 / 105 / 113            119 / 105 / 113
+//   2                   201 / 171 / 186            202 / 194 / 187
+//   4                   368 / 313 / 347            369 / 354 / 348
+//   6                   540 / 536 / 522            540 / 531 / 521
+// The MLP set to FP8 (125 MB, 267 MB out): 181 / 168 / 176 and 182 / 178 / 177.  The
+// payload's line is three eighths of the cache, which three such sets overfill: above it
+// sets decoded in turn (a model's layers one after the other) gain from streaming it,
+// below it the gain of a set decoded again and again is the larger.
+// Just above the output's line a reader that follows at once takes back what the
+// decode gained (one block and a sum over it: 241 / 244 / 244; two: 468 / 451 / 449); below it the
+// reader gains more: an INT8 down projection (0.16 GB) followed by its product loses 5 us
+// when its weights are streamed.
+constexpr uint64_t kCacheBytes = 256ull << 20, kCachePayloadBytes = kCacheBytes / 8 * 3;
 
 void use_streaming(std::vector<LayerDev>& D) {
-  uint64_t bytes = 0;
+  uint64_t out = 0, payload = 0;
   for (const LayerDev& d : D) {
     const uint64_t w = d.out_dtype == EP_BF16 || d.out_dtype == EP_FP16 ? 2
                        : d.out_dtype == EP_FP32 || d.out_dtype == EP_COORD2_I32 ? 4 : 1;
     const uint64_t tiles = d.tile_end - d.tile_begin;
-    bytes += w * 8 * d.V * tiles + (uint64_t)d.pay_bytes * tiles / std::max<uint32_t>(1, d.n_tiles);
+    out += w * 8 * d.V * tiles;
+    payload += (uint64_t)d.pay_bytes * tiles / std::max<uint32_t>(1, d.n_tiles);
   }
-  for (LayerDev& d : D) d.stream = bytes > kCacheBytes ? 1u : 0u;
+  const uint32_t stream = out + payload <= kCacheBytes ? 0
+                          : payload <= kCachePayloadBytes ? kStreamOutput : kStreamOutput | kStreamPayload;
+  for (LayerDev& d : D) d.stream = stream;
 }
 
 int decode_tiles(const ep_tensor_info* info, const void* d_blob, int out_dtype, void* d_out,

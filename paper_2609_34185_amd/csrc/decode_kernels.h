@@ -60,6 +60,8 @@ constexpr uint32_t kStateLow = 1u << 15;
 // decoded INT8 container values are multiplied into a small int8 batch X and
 // summed into Y (int32) instead of being stored.
 constexpr int kOutDotI8 = 0x200;
+// What of a launch's traffic bypasses the caches (LayerDev::stream).
+constexpr uint32_t kStreamOutput = 1, kStreamPayload = 2;
 constexpr int kAnyType = 0;   // template argument: the output type is read from the layer
 constexpr uint32_t kDotMaxTokens = 8;
 
@@ -103,7 +105,7 @@ struct LayerDev {
   uint32_t tpt;                   // tiles per task: 4 (two chains per wave) or 2 (one chain)
   uint32_t g_bits, g_meta;        // global-table path: log2 G, byte offset of its metadata
   uint32_t compact;               // search path: the compact form may be tried
-  uint32_t stream;                // four-tile steady state: payload and output bypass the caches
+  uint32_t stream;                // four-tile slot-table steady state: kStream* bits
   const uint8_t* tables;          // prepared stacks: the layer's decode tables as built in LDS
                                   // (ring_offset bytes), copied in instead of rebuilt; or null
 };
@@ -1772,9 +1774,10 @@ __device__ __forceinline__ int32_t half_sum(int32_t v) {
 // used once the vector's first four weights are known (after field 4), when
 // columns 4-7 are requested, used at the end of the round.
 // Without TWO every vector is added to Y on its own.
-template <int B, int DT, bool SAT, bool TWO, bool WIDE, int MT = 1, bool STREAM = false>
+template <int B, int DT, bool SAT, bool TWO, bool WIDE, int MT = 1, uint32_t STREAM = 0>
 __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ring_area, uint32_t t0,
                                          int32_t* status) {
+  constexpr bool PAY = (STREAM & kStreamPayload) != 0;
   const uint32_t lane = threadIdx.x & 63, wave = wave_id();
   const uint32_t half = lane >> 5, l = lane & 31;
   const EP_GLOBAL uint32_t* states = gptr<const uint32_t>(L.blob + L.off_states);
@@ -1832,8 +1835,8 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
   u32x2 pend0, pend1, pendB0, pendB1;
 #pragma unroll
   for (int i = 0; i < 5; i++) o[i] = uni(o[i]);
-  const u32x4 fill0 = fast_start<STREAM>(F0, pend0, rsrc, half, l, o[0], o[1], o[1], o[2]);
-  const u32x4 fill1 = fast_start<STREAM>(F1, pend1, rsrc, half, l, o[2], o[3], o[3], o[4]);
+  const u32x4 fill0 = fast_start<PAY>(F0, pend0, rsrc, half, l, o[0], o[1], o[1], o[2]);
+  const u32x4 fill1 = fast_start<PAY>(F1, pend1, rsrc, half, l, o[2], o[3], o[3], o[4]);
   // One wait for everything requested so far, so that no load is in flight
   // when the loop starts (the loop's own waits then stay one round behind).
   __builtin_amdgcn_s_waitcnt(0);
@@ -1865,7 +1868,7 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
       xsave[1] = x[1];
     }
     // room for a block: margin <= ring - block
-    fast_stage_both<STREAM>(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half,
+    fast_stage_both<PAY>(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half,
                     kFastRingWords - kFastBlockWords + 1);
     float sg[2], hc[2];
 #pragma unroll
@@ -1914,7 +1917,7 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
   q_take<DT, I, WIDE>(acc[0], e0, y0, cb[0] >> (B + 5));                                      \
   q_take<DT, I, WIDE>(acc[1], e1, y1, cb[1] >> (B + 5));
     EP_FIELD(1) EP_FIELD(2)
-    fast_stage_both<STREAM>(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
+    fast_stage_both<PAY>(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
     EP_FIELD(3) EP_FIELD(4)
     if constexpr (ACC) {
 #pragma unroll
@@ -1927,7 +1930,7 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
       }
     }
     EP_FIELD(5)
-    fast_stage_both<STREAM>(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
+    fast_stage_both<PAY>(F0, F1, pend0, pendB0, pend1, pendB1, lds, vrb08, vrb18, vl8, rsrc, half, 3 * 32);
     EP_FIELD(6) EP_FIELD(7) EP_FIELD(8)
 #undef EP_FIELD
 #undef EP_PIN
@@ -1945,8 +1948,8 @@ __device__ __forceinline__ void lut_task(const Hot& L, uint8_t* lds, uint32_t ri
       }
     } else {
       if (!PART || !pin) {
-        q_put<DT, STREAM>(obase, voff[0], acc[0]);
-        q_put<DT, STREAM>(obase, voff[1], acc[1]);
+        q_put<DT, (STREAM & kStreamOutput) != 0>(obase, voff[0], acc[0]);
+        q_put<DT, (STREAM & kStreamOutput) != 0>(obase, voff[1], acc[1]);
       }
       obase += 32 * VB;
     }
@@ -2321,7 +2324,7 @@ __device__ __forceinline__ void search_task(const Hot& L, uint8_t* lds, uint32_t
 }
 
 // Row-scale and sum variants of a full four-tile slot-table task.
-template <int B, int DT, bool SAT, bool WIDE, bool STREAM = false>
+template <int B, int DT, bool SAT, bool WIDE, uint32_t STREAM = 0>
 __device__ __forceinline__ void lut_task_rows(const Hot& L, uint8_t* lds, uint32_t ring_area,
                                               uint32_t t0, int32_t* status) {
   if constexpr (DT == kOutDotI8) {
@@ -2365,7 +2368,9 @@ __device__ __forceinline__ bool lut_task_any(const Hot& L, uint8_t* lds, uint32_
   } else {
     auto plain = [&](auto dt) {
       constexpr int DT = decltype(dt)::value;
-      if (L.stream) lut_task_rows<B, DT, false, WIDE, true>(L, lds, ring_area, t0, status);
+      constexpr uint32_t BOTH = kStreamOutput | kStreamPayload;
+      if (L.stream == BOTH) lut_task_rows<B, DT, false, WIDE, BOTH>(L, lds, ring_area, t0, status);
+      else if (L.stream) lut_task_rows<B, DT, false, WIDE, kStreamOutput>(L, lds, ring_area, t0, status);
       else lut_task_rows<B, DT, false, WIDE>(L, lds, ring_area, t0, status);
     };
     switch (L.out_dtype) {

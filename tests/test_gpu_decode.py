@@ -653,6 +653,34 @@ def test_launch_larger_than_the_last_level_cache(E, oracle, name, container):
         assert all(np.array_equal(dq[i].cpu().numpy(), ref_dq) for i in range(n))
 
 
+@pytest.mark.parametrize("name,container", [("BF16", 0), ("FP8", 1), ("INT8", 2)])
+def test_launch_whose_payload_leaves_the_cache(E, oracle, name, container):
+    """Above 96 MiB of payload its loads are streaming too: just below and just above that line,
+    tiles of whole and of partial rounds, against the oracle's decode of the one blob."""
+    w = W.draw_tensor(np.random.default_rng(12), 1501, 2056, **W.CFG3)
+    ecode, ocode = codes(E, oracle, name)
+    for V in (512, 500):
+        blob, _ = oracle.encode(w, 6.0, container=container, tile_vectors=V)
+        info = E.blob_info(blob)
+        ref, _ = oracle.decode(blob, ocode)
+        d_blob = E.to_device(blob)
+        line = (96 << 20) // (2 * info.payload_words)
+        out = torch.empty((line + 1, 1501, 2056), dtype=E.torch_dtype(ecode), device="cuda")
+        bits = out.view(torch.int16 if out.element_size() == 2 else torch.uint8)
+        dq = torch.zeros(1501, dtype=torch.float32, device="cuda")
+        st = torch.zeros(1, dtype=torch.int32, device="cuda")
+        ws = torch.zeros(E.decode_layers_workspace(line + 1), dtype=torch.uint8, device="cuda")
+        for n in (line, line + 1):
+            say(f"  {n} layers, V = {V}, b = {info.prob_bits}, path = {info.path} -> {name}")
+            bits.fill_(0x55)
+            E.decode_layers([(info, d_blob.data_ptr(), out[i].data_ptr(), dq.data_ptr(), ecode) for i in range(n)],
+                            ws.data_ptr(), ws.numel(), st.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert int(st.item()) == 0
+            assert np.array_equal(gpu_bits(out[0]), ref)
+            assert all(bool((bits[i] == bits[0]).all()) for i in range(1, n))
+
+
 def observed_symbols(blob):
     """Symbols with a positive frequency over a blob's 16 field tables."""
     at, n = 48 + 4, 0
