@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kThreads) void decode_gemm_kernel(const GemmLaunch 
   saturate_conversions();
   const LayerDev& L = A.L;
   const GemmArgs& g = A.g;
-  if (L.tables) load_tables<PATH>(L, lds);   // prepared by ep_decode_gemm_prepare
+  if (__builtin_expect(L.tables != nullptr, 1)) load_tables<PATH>(L, lds);   // prepared by ep_decode_gemm_prepare
   else build_tables<PATH>(L, lds);
   __syncthreads();
   const uint32_t ring_area = uni(ring_offset<PATH>(L));

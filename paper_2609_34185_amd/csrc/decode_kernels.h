@@ -106,6 +106,7 @@ struct LayerDev {
   uint32_t g_bits, g_meta;        // global-table path: log2 G, byte offset of its metadata
   uint32_t compact;               // search path: the compact form may be tried
   uint32_t stream;                // four-tile slot-table steady state: kStream* bits
+  uint32_t dense;                 // slot tables: filled symbol by symbol (see build_lut)
   const uint8_t* tables;          // prepared stacks: the layer's decode tables as built in LDS
                                   // (ring_offset bytes), copied in instead of rebuilt; or null
 };
@@ -439,6 +440,17 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
   return v;
 }
 
+// The frequencies of the wave's table and its index range.
+struct FieldTable {
+  const EP_GLOBAL uint16_t* f;
+  uint32_t A;
+};
+
+__device__ __forceinline__ FieldTable table_of(const LayerDev& L) {
+  const uint32_t t = wave_id();
+  return FieldTable{gptr<const uint16_t>(L.blob + L.tab_off[t]), uni(L.tab_A[t])};
+}
+
 // Prefix sums of the wave's table's frequencies: put(s, F_s, f_s, i) for every
 // symbol s of its index range, where i counts the symbols of positive frequency
 // before s.  Returns their number; `total` gets the sum of the frequencies (2^b,
@@ -449,10 +461,9 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
 // Lanes past the end read the table's last entry (in bounds) and use 0.
 constexpr int kScanAhead = 4;
 template <class Put>
-__device__ __forceinline__ uint32_t scan_table(const LayerDev& L, Put put, uint32_t& total) {
-  const uint32_t lane = threadIdx.x & 63, t = wave_id();
-  const EP_GLOBAL uint16_t* f = gptr<const uint16_t>(L.blob + L.tab_off[t]);
-  const uint32_t A = uni(L.tab_A[t]);
+__device__ __forceinline__ uint32_t scan_table(const FieldTable& T, Put put, uint32_t& total) {
+  const uint32_t lane = threadIdx.x & 63, A = T.A;
+  const EP_GLOBAL uint16_t* const f = T.f;
   uint32_t run = 0, n = 0, fa[kScanAhead], fb[kScanAhead];
   auto fetch = [&](uint32_t g0, uint32_t* v) {
 #pragma unroll
@@ -2448,7 +2459,7 @@ __device__ __forceinline__ uint32_t build_compact(const LayerDev& L, uint32_t* l
   const int32_t mn = L.tab_min[t], zs = (t & 7) == 7 ? 1 : 0;   // field 8 stores 2m
   uint16_t* const row = reinterpret_cast<uint16_t*>(lds) + compact_buckets(area, k) / 2 + (t << k);
   uint32_t sum = 0;
-  const uint32_t n = scan_table(L, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t i) {
+  const uint32_t n = scan_table(table_of(L), [&](uint32_t s, uint32_t F, uint32_t f, uint32_t i) {
     if (!f) return;
     lds[at + i] = F | ((uint32_t)(((int32_t)s + mn) << zs) << 16);
     const uint32_t j1 = (F + f + (1u << sh) - 1) >> sh;
@@ -2469,7 +2480,7 @@ __device__ __forceinline__ void build_search(const LayerDev& L, uint32_t* lds) {
   uint16_t* const cum = reinterpret_cast<uint16_t*>(lds) + L.tab_base[t] + t;
   uint16_t* const bk = reinterpret_cast<uint16_t*>(lds) + S.bucket / 2 + t * n1;
   uint32_t sum = 0;
-  scan_table(L, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t) {
+  scan_table(table_of(L), [&](uint32_t s, uint32_t F, uint32_t f, uint32_t) {
     cum[s] = (uint16_t)F;
     const uint32_t j0 = (F + (1u << shift) - 1) >> shift, j1 = (F + f + (1u << shift) - 1) >> shift;
     for (uint32_t j = j0; j < j1; j++) bk[j] = (uint16_t)s;
@@ -2496,7 +2507,7 @@ __device__ __forceinline__ void build_global(const LayerDev& L, uint32_t* lds) {
   const uint32_t g = L.g_bits, G = 1u << g;
   uint16_t* const cum = reinterpret_cast<uint16_t*>(lds) + global_base(L, wave_id());
   uint32_t sum = 0;
-  scan_table(L, [&](uint32_t s, uint32_t F, uint32_t, uint32_t) {
+  scan_table(table_of(L), [&](uint32_t s, uint32_t F, uint32_t, uint32_t) {
     if ((s & (G - 1)) == 0) cum[s >> g] = (uint16_t)F;
   }, sum);
   if (threadIdx.x < 64) {
@@ -2508,35 +2519,42 @@ __device__ __forceinline__ void build_global(const LayerDev& L, uint32_t* lds) {
   }
 }
 
-// The slot tables are filled from the symbols that occur, collected in the ring
-// area: each table's where its index range would start, or, when the ranges
-// together are larger than the area, in a sixteenth of it (wide tables at 6 bits
-// per weight: ranges of 9,600 in all, 420 symbols in the largest table).
+// Wide slot tables of a dense tensor (LayerDev::dense: many symbols, each of few
+// slots): every lane fills the slots of its own symbol straight from the prefix sums, a
+// chunk of 64 symbols taking as many steps as its largest frequency.  At lower rates that is
+// hundreds of steps; there, and for narrow entries, the tables are filled slot by slot from
+// the symbols that occur, collected in the ring area: each table's where its index range
+// would start, or, when the ranges together are larger than the area, in a sixteenth of it.
+//
+// A launch of two tiles, us, symbol by symbol / slot by slot: 4.0 bits per weight 32 / 25, 5.0
+// 25 to 30 / 26, 5.5 24 to 29 / 26, 5.8 23 / 27, 6.6 23 / 26; a decode of 17408 x 5120 to INT8
+// at 6 bits 82.1 / 85.4.
 template <bool WIDE>
 __device__ __forceinline__ void build_lut(const LayerDev& L, uint32_t* lds) {
   constexpr uint32_t kRoom = kRingBytes / 4;
   const uint32_t t = wave_id();
+  const FieldTable T = table_of(L);   // read with the rest of the descriptor, before the branch waits for it
   const bool ranges = uni(L.sum_A) <= kRoom;
   uint32_t* const sym = lds + (16u << L.b) + (ranges ? uni(L.tab_base[t]) : t * (kRoom / 16));
   const uint32_t room = ranges ? kRoom : kRoom / 16;
   uint32_t sum = 0;
-  const uint32_t n = scan_table(L, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t i) {
-    if (f && i < room) sym[i] = F | ((f - 1) << 11) | (s << 22);
-  }, sum);
-  if (n <= room) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's own writes: no barrier
-    fill_lut_table<WIDE>(L, lds, sym, n);
-  } else {
-    // more symbols than the room holds: every lane fills the slot range of its own
-    // symbol straight from the prefix sums
-    uint32_t* const row = lds + (t << L.b);
-    const int32_t mn = L.tab_min[t], zs = (t & 7) == 7 ? 1 : 0;
-    scan_table(L, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t) {
-      const uint32_t z = (uint32_t)(((int32_t)s + mn) << zs);
-      for (uint32_t i = 0; i < f; i++)
-        row[F + i] = WIDE ? (f - 1) | (i << 11) | ((z & 0x3FF) << 22) : f | (i << 12) | ((z & 0xFF) << 24);
+  if (!WIDE || !uni(L.dense)) {
+    const uint32_t n = scan_table(T, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t i) {
+      if (f && i < room) sym[i] = F | ((f - 1) << 11) | (s << 22);
     }, sum);
+    if (n <= room) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's own writes: no barrier
+      fill_lut_table<WIDE>(L, lds, sym, n);
+      return;
+    }
   }
+  uint32_t* const row = lds + (t << L.b);
+  const int32_t mn = L.tab_min[t], zs = (t & 7) == 7 ? 1 : 0;
+  scan_table(T, [&](uint32_t s, uint32_t F, uint32_t f, uint32_t) {
+    const uint32_t z = (uint32_t)(((int32_t)s + mn) << zs);
+    for (uint32_t i = 0; i < f; i++)
+      row[F + i] = WIDE ? (f - 1) | (i << 11) | ((z & 0x3FF) << 22) : f | (i << 12) | ((z & 0xFF) << 24);
+  }, sum);
 }
 
 template <int PATH>

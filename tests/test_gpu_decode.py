@@ -180,6 +180,27 @@ def test_wide_slot_entries(E, oracle, b):
                 check_blob(E, oracle, blob, tag=f"wide{b} {tasks}")
 
 
+@pytest.mark.parametrize("b,spread", [(9, 0.0), (10, 0.0), (11, 0.0), (11, 0.75)])
+def test_wide_tables_on_both_sides_of_the_fill_rule(E, oracle, b, spread):
+    """Wide slot tables are filled symbol by symbol from 5.7 bits per weight on, slot by slot
+    below: rates on either side of that line, with index ranges that fit the scratch area
+    together and (a few vectors far out) ranges that do not."""
+    w = (W.ragged_tensor(93, 96, 4096).astype(np.uint32) << 16).view(np.float32).copy()
+    if spread:
+        rng = np.random.default_rng(93)
+        for r in range(40):
+            w[r, 8 * r:8 * r + 8] = rng.uniform(-spread, spread, 8)
+    sides = set()
+    for target in (5.4, 5.95, 6.05, 6.4):
+        blob, _ = oracle.encode(w, target, prob_bits=b)
+        info = E.blob_info(blob)
+        dense = 10 * (16 * info.payload_words + 256 * info.n_tiles) >= 57 * info.rows * info.cols
+        sides.add((dense, info.sum_alphabet > 8192))
+        check_blob(E, oracle, blob, dtypes=["COORD2", "BF16"], tag=f"fill {target} b={b}", path=3)
+    assert {d for d, _ in sides} == {False, True}
+    assert not spread or (False, True) in sides
+
+
 def escalated_blobs(oracle):
     """Two blobs of App. C.1's precision escalation, from a tensor whose sampled rows miss
     large values in the other rows: at 10 bpp the alphabet escalates b to 13 (bucketed search
