@@ -1496,16 +1496,18 @@ __device__ __forceinline__ void field_step2_c(const Hot& L, const uint32_t* tab,
 // word at P plus the number of refilling lanes below it in its half (v_mbcnt
 // over the ballot's lower word for lanes 0-31 only, then over its upper
 // word) and advances P by the popcount of its own half of the ballot while the
-// word is in flight.  A step of a wave alone on its SIMD takes 189 cycles, two
-// LDS round trips of 56 cycles among them; a whole decode, rounds' overhead
-// included, went from 106 to 88 ns a step (3072^2 to FP16: 36.6 -> 32.1 us,
-// 10240 x 3840 at 1820-vector tiles to BF16: 106 -> 83 us).
+// word is in flight.  Launches that fill the SIMDs (products with five to eight rows
+// of X, small launches near their limit) are bound by issue instead, so the refill has
+// ten vector instructions (with twelve, the product of 5120 x 17408 with six rows at
+// 128-vector tiles and 4.2 bits took 133.4 us, not 131.4, and more than with the scalar
+// positions at 6.8 bits).  Nine, with the refilled lanes taken by EXEC and not by a
+// select, gain another 1 to 3 % there and lose 1 % on a wave alone on its SIMD.
 // An SGPR that a vector instruction wrote may be read as a vector operand two
 // wait states later at the earliest (gfx940 and up); FILL is one instruction of
 // the step's own work in the second of them.
 #define EP_REFILL_ONE_W(FILL, WORK)                                         \
   "v_cmp_gt_u32_e32 vcc, 0x8000, %[x0]\n\t"                                 \
-  "v_lshlrev_b32_e32 %[xs], 16, %[x0]\n\t"                                  \
+  "s_nop 0\n\t"                                                             \
   FILL                                                                     \
   "v_and_b32_e32 %[u0], vcc_lo, %[mlo]\n\t"                                 \
   "v_mbcnt_lo_u32_b32 %[t0], %[u0], %[P]\n\t"                               \
@@ -1513,19 +1515,17 @@ __device__ __forceinline__ void field_step2_c(const Hot& L, const uint32_t* tab,
   "v_lshlrev_b32_e32 %[t0], 1, %[t0]\n\t"                                   \
   "v_and_or_b32 %[t0], %[t0], %[rmask], %[vrb0]\n\t"                        \
   "ds_read_u16 %[w0], %[t0]\n\t"                                            \
-  "v_and_b32_e32 %[g0], vcc_hi, %[mhi]\n\t"                                 \
-  "v_bcnt_u32_b32 %[P], %[u0], %[P]\n\t"                                    \
+  "v_and_or_b32 %[g0], vcc_hi, %[mhi], %[u0]\n\t"                           \
   "v_bcnt_u32_b32 %[P], %[g0], %[P]\n\t"                                    \
   WORK                                                                     \
   "s_waitcnt lgkmcnt(0)\n\t"                                                \
-  "v_or_b32_e32 %[w0], %[xs], %[w0]\n\t"                                    \
+  "v_lshl_or_b32 %[w0], %[x0], 16, %[w0]\n\t"                               \
   "v_cndmask_b32_e32 %[x0], %[x0], %[w0], vcc\n\t"
 
 #define EP_STEP1_OUTS                                                                    \
-  [x0] "+v"(x0), [P] "+v"(P), [u0] "=&v"(u0), [g0] "=&v"(g0), [t0] "=&v"(t0), [w0] "=&v"(w0), \
-      [xs] "=&v"(xs)
+  [x0] "+v"(x0), [P] "+v"(P), [u0] "=&v"(u0), [g0] "=&v"(g0), [t0] "=&v"(t0), [w0] "=&v"(w0)
 
-#define EP_STEP1_TEMPS uint32_t u0, g0, t0, w0, xs
+#define EP_STEP1_TEMPS uint32_t u0, g0, t0, w0
 
 #define EP_STEP1_INS                                                                     \
   [mlo] "v"(mlo), [mhi] "v"(~mlo), [vrb0] "v"(vrb0), [rmask] "s"(kOneRingBytes - 1),      \
