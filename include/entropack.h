@@ -384,9 +384,9 @@ typedef struct {
   void* d_workspace;         /* device descriptor list (caller-owned memory) */
   int32_t n_layers;
   uint32_t path;             /* decode path shared by all layers, or 15 for a list of several */
-  uint32_t total_tasks;      /* 4-tile tasks over all layers */
+  uint32_t total_tasks;      /* tasks over all layers (of four tiles each, or of two: see above) */
   uint32_t lds_bytes;        /* LDS of the launch */
-  uint32_t reserved[4];
+  uint32_t reserved[4];      /* [0]: workgroups of a launch whose layers have their own, else 0 */
 } ep_stack;
 
 /* Device bytes ep_stack_prepare needs for n layers: the descriptors and one

@@ -27,11 +27,11 @@ typedef __bf16 v8bf_t __attribute__((ext_vector_type(8)));
 //
 // A wave's slice of K is a short chain of loads from L2 and beyond (the slab was
 // written by other waves of its CU, X by anyone), so it is bound by their
-// latency: kDepth groups of fragments are in flight, as many as the registers
-// hold (with 88 registers' worth of fragments, 132 to 180 bytes a lane spill and
-// the product with 16 rows loses what it gained; with 64, 48 to 64 bytes).  Down
-// projection with 16 rows of X: 121 -> 112 us; DiT MLP input (BF16) with 64 rows:
-// 104.6 -> 83.5 us, the clearing launch and the atomics gone among it.
+// latency: kDepth groups of fragments are in flight, two or three by the shape, with
+// 64 registers' worth of fragments and sums (88 spill 132 to 180 bytes a lane and the
+// product with 16 rows loses what it gained; 64 spill 36 to 56).  Sums in LDS
+// instead of a clearing launch and atomics, and kernels of one output type: down
+// projection with 16 rows of X 121 -> 112 us, DiT MLP input (BF16) with 64 rows 104.6 -> 83.5 us.
 //
 // BF: the BF16 product (bf16 X and slab, v_mfma_f32_16x16x32_bf16, fp32 Y).
 // A lane's 16 bytes of a 64-byte K step are then 8 bf16 elements, the same
@@ -47,12 +47,11 @@ __device__ __forceinline__ void block_product_nt(const LayerDev& L, const GemmAr
   const uint32_t slice = I >= kWavesPerGroup ? 0u : wave / I;
   const uint32_t it0 = I >= kWavesPerGroup ? wave : wave % I;
   // 64-byte K steps per group, and groups in flight: kDepth (XT + NT) kGroup
-  // fragments of 4 VGPRs and the accumulators stay within the registers that one
+  // fragments of 4 VGPRs and the accumulators in 64 of the 128 registers that one
   // wave of four on a SIMD has
   constexpr uint32_t kGroup = XT + NT <= 3 ? 2 : 1;
-  constexpr uint32_t kFit = (64 - 4 * XT * NT) / (4 * kGroup * (XT + NT));
-  constexpr uint32_t kDepth = kFit < 4 ? kFit : 4;
-  static_assert(kDepth >= 2, "two groups in flight at least");
+  constexpr uint32_t kDepth = (64 - 4 * XT * NT) / (4 * kGroup * (XT + NT));
+  static_assert(kDepth == 2 || kDepth == 3, "groups in flight");
   constexpr uint32_t kStep = 64 * kGroup;
   // slices are cut at 128-byte boundaries whatever the group
   const uint32_t groups = (C + 127) / 128, gper = (groups + S - 1) / S;

@@ -590,9 +590,9 @@ __global__ __launch_bounds__(256) void k_select(const int32_t* cand, uint64_t ca
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-// Blocks of k_quantize: one group of vectors each up to eight blocks a CU (the
-// search steps' samples), then more groups each, so that the extents are reduced
-// once per wave and not per group.
+// Blocks of k_quantize: one group of vectors each up to 2,048 blocks (eight on each
+// of 256 CUs; the search steps' samples), then more groups each, so that the extents are
+// reduced once per wave and not per group.
 unsigned quantize_blocks(int64_t nv) {
   return (unsigned)std::min<int64_t>((nv + kQuantizeThreads - 1) / kQuantizeThreads, 2048);
 }

@@ -647,7 +647,7 @@ def test_config4_full_stack_sampled_tiles(E, oracle):
 
 @pytest.mark.parametrize("name,container", [("FP32", 0), ("FP16", 0), ("FP8", 1), ("INT8", 2)])
 def test_launch_larger_than_the_last_level_cache(E, oracle, name, container):
-    """A list of layers that moves more than 256 MiB takes the streaming stores and loads: one
+    """A list of layers that moves more than 256 MiB takes the streaming stores (FP32 none): one
     blob decoded into as many outputs as that needs, each equal to the oracle's decode.  BF16
     and the full-size FP8 set are streamed by the configuration tests."""
     w = W.draw_tensor(np.random.default_rng(11), 1500, 2048, **W.CFG3)
